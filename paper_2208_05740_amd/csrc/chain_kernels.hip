@@ -178,14 +178,14 @@ __global__ void __launch_bounds__(NW * 64) chain_opt_kernel(ChainArgs a) {
     int cur = 0;
     {
       const ChainNode& n = a.nodes[L - 1];
-      BoundEpi<T> epi{BoundEpiArgs{n.nd, n.cc, a.rp, nullptr, nullptr, n.ahat}};
+      BoundEpi<T> epi{BoundEpiArgs{n.nd, n.cc, a.rp, nullptr, 0, nullptr, n.ahat}};
       chain_top<T>(epi, LdsSink<T>{off[cur], m0, a.P}, a.chat, a.chat_ld, a.rp.S, m0, M, n.nd.size);
     }
     __syncthreads();
     for (int i = L - 2; i >= 0; --i) {
       const ChainNode& up = a.nodes[i + 1];   // Lambda^(i+1) in LDS, pushed through node i+1's in-edge
       const ChainNode& n = a.nodes[i];
-      BoundEpi<T> epi{BoundEpiArgs{n.nd, n.cc, a.rp, nullptr, nullptr, n.ahat}};
+      BoundEpi<T> epi{BoundEpiArgs{n.nd, n.cc, a.rp, nullptr, 0, nullptr, n.ahat}};
       chain_layer<T, NW, TN, false, D>(epi, LdsSink<T>{off[cur ^ 1], m0, a.P}, m0, M, n.nd.size, up.nd.size, off[cur],
                                        a.P, (const T*)up.WT, up.ldWT);
       __syncthreads();

@@ -51,6 +51,23 @@ template <> struct Op<float> {
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
   }
+  // mma of R fragments into acc[.][k], the R independent products of a step
+  // side by side (the four steps of one product depend on each other)
+  template <int R, int TN>
+  __device__ static inline void mma_rows(const uint4 (&a)[R], const uint4& b, f4 (&c)[R][TN], int k) {
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      c[q][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q].x), __uint_as_float(b.x), c[q][k], 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      c[q][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q].y), __uint_as_float(b.y), c[q][k], 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      c[q][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q].z), __uint_as_float(b.z), c[q][k], 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      c[q][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q].w), __uint_as_float(b.w), c[q][k], 0, 0, 0);
+  }
 };
 template <> struct Op<bf16> {
   static constexpr int VEC = 8;
@@ -59,6 +76,11 @@ template <> struct Op<bf16> {
     bf16x8 av = __builtin_bit_cast(bf16x8, a);
     bf16x8 bv = __builtin_bit_cast(bf16x8, b);
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+  }
+  template <int R, int TN>
+  __device__ static inline void mma_rows(const uint4 (&a)[R], const uint4& b, f4 (&c)[R][TN], int k) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) mma(a[q], b, c[q][k]);
   }
 };
 
@@ -81,6 +103,17 @@ __device__ inline uint4 mask_tail(uint4 v, int keep) {
   for (int q = 0; q < (int)(16 / sizeof(T)); ++q)
     if (q >= keep) e[q] = to_t<T>(0.f);
   return *(const uint4*)e;
+}
+
+// ------------------------------------------------------------------ workgroup order
+// XCD-aware tile order: workgroups are dispatched round-robin over the 8
+// XCDs by linear id, so the ids an XCD receives map onto a contiguous run of
+// tiles (row panel major) and all column tiles of a row panel share that
+// XCD's L2 instead of fetching the A panel once per XCD.
+__device__ inline int xcd_tile(int id, int total) {
+  const int xcd = id % 8, kx = id / 8;
+  const int per = total / 8, rem = total % 8;
+  return xcd * per + (xcd < rem ? xcd : rem) + kx;
 }
 
 // ------------------------------------------------------------------ output sinks
@@ -237,6 +270,13 @@ __device__ inline float adam_step(float lr, float mm, float vv, float ibc1, floa
   return lr * (mm * ibc1) * __builtin_amdgcn_rcpf(sqrtf(vv * ibc2) + eps);
 }
 
+// an accumulated value added to the GEMM's (fp32, or the operand type when acc_t)
+template <typename T>
+__device__ inline float acc_at(const void* acc, int acc_t, size_t i) {
+  if (sizeof(T) == 2 && acc_t) return from_t<T>(((const T*)acc)[i]);
+  return ((const float*)acc)[i];
+}
+
 // effective class and split slot of each element (row, neuron)
 template <int R>
 __device__ inline void split_class(const RowParams& rp, int rank, int cls, int rc, int* c, int* slot) {
@@ -264,6 +304,7 @@ struct BoundEpi {
     float al[TN][R];     // alpha (unstable) or 0
     float rh[TN][PI ? R : 1];   // rho (PI only)
     int8_t c[TN][R];     // effective class
+    int uk[TN][PE ? R : 1];   // column of a_hat (rank within the node), -1: not kept
   };
   static constexpr bool kColPre = true;
   __device__ inline const NodeDev& col_node() const { return a.nd; }
@@ -294,10 +335,11 @@ struct BoundEpi {
         const float4 nr = nd.rec[j];
         f.lj[k][q] = nr.x; f.uj[k][q] = nr.y; f.iul[k][q] = nr.z; f.bj[k][q] = nr.w;
         kv[k][q] = (!PE && pre) ? pre->kind[k] : nd.kind[j];
+        f.uk[k][q] = kind_rank(kv[k][q]) >= 0 ? kind_rank(kv[k][q]) - nd.rank0 : -1;
       }
 #pragma unroll
       for (int q = 0; q < R; ++q)
-        f.aoff[k][q] = a.acc_in ? a.acc_in[(size_t)f.rc[q] * nd.ld + jq[k][GCP_QC(q)]] : 0.f;
+        f.aoff[k][q] = a.acc_in ? acc_at<T>(a.acc_in, a.acc_t, (size_t)f.rc[q] * nd.ld + jq[k][GCP_QC(q)]) : 0.f;
     }
 #pragma unroll
     for (int k = 0; k < TN; ++k)
@@ -323,12 +365,35 @@ struct BoundEpi {
       }
     }
   }
+  // Lambda and the row constant's part of one element of class c: tadd the
+  // additions to Lambda, sq = gamma^T Q, al alpha, rho the explicit pi
+  __device__ static inline void relax(int c, float ah, float tadd, float sq, float al, float lj, float uj, float iul,
+                                      float rho, float& lam, float& konst) {
+    if (c == ACTIVE) {                           // x_hat = x, z = 1
+      lam = ah + tadd;
+      konst = sq;
+    } else if (c == INACTIVE) {                  // x_hat = 0, z = 0
+      lam = tadd;
+      konst = 0.f;
+    } else {                                     // Lemma A.1, C = [-a_hat]_+, q = -s
+      const float n = fmaxf(-ah, 0.f), p = fmaxf(ah, 0.f);
+      float pi, h;
+      if constexpr (PI) {                        // h(pi) = l pi - [u (n - pi) + l pi - s]_+
+        pi = rho * n;
+        h = lj * pi - fmaxf(uj * n - (uj - lj) * pi - sq, 0.f);
+      } else if (sq >= uj * n) { pi = 0.f; h = 0.f; }
+      else if (sq <= lj * n) { pi = n; h = sq; }
+      else { pi = (uj * n - sq) * iul; h = lj * pi; }
+      lam = al * p - pi + tadd;
+      konst = h;
+    }
+  }
   template <int R, int TN, bool PE>
   __device__ inline void apply(const Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc,
                                const float (&val)[TN][R], double (&rs)[R], int M, int N) const {
     apply_to<R, TN, PE>(f, lc, val, rs, M, N, GlobalSink<T>{(T*)a.lam_out});
   }
-  // Lambda goes to `lam`; a_hat (if kept) to a.ahat_out
+  // Lambda goes to `lam_sink`; a_hat of unstable neurons (if kept) to a.ahat_out
   template <int R, int TN, bool PE, class Sink>
   __device__ inline void apply_to(const Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc,
                                   const float (&val)[TN][R], double (&rs)[R], int M, int N, const Sink& lam_sink) const {
@@ -340,29 +405,12 @@ struct BoundEpi {
         const int qc = GCP_QC(q);
         const float ah = val[k][q] + f.aoff[k][q];   // a_hat = Lambda^(i+1) W + gamma^T G
         float lam, konst;
-        if (f.c[k][q] == ACTIVE) {                   // x_hat = x, z = 1
-          lam = ah + f.tadd[k][q];
-          konst = f.sQ[k][q];
-        } else if (f.c[k][q] == INACTIVE) {          // x_hat = 0, z = 0
-          lam = f.tadd[k][q];
-          konst = 0.f;
-        } else {                                     // Lemma A.1, C = [-a_hat]_+, q = -s
-          const float n = fmaxf(-ah, 0.f), p = fmaxf(ah, 0.f), sq = f.sQ[k][q];
-          float pi, h;
-          if constexpr (PI) {                        // h(pi) = l pi - [u (n - pi) + l pi - s]_+
-            const float uj = f.uj[k][qc], lj = f.lj[k][qc];
-            pi = f.rh[k][q] * n;
-            h = lj * pi - fmaxf(uj * n - (uj - lj) * pi - sq, 0.f);
-          } else if (sq >= f.uj[k][qc] * n) { pi = 0.f; h = 0.f; }
-          else if (sq <= f.lj[k][qc] * n) { pi = n; h = sq; }
-          else { pi = (f.uj[k][qc] * n - sq) * f.iul[k][qc]; h = f.lj[k][qc] * pi; }
-          lam = f.al[k][q] * p - pi + f.tadd[k][q];
-          konst = h;
-        }
+        relax(f.c[k][q], ah, f.tadd[k][q], f.sQ[k][q], f.al[k][q], f.lj[k][qc], f.uj[k][qc], f.iul[k][qc],
+              PI ? f.rh[k][PI ? q : 0] : 0.f, lam, konst);
         if (f.ev[k][q]) {
           const size_t ij = (size_t)f.rc[q] * nd.ld + lc.j[k][qc];
           lam_sink(ij, f.rc[q], lc.j[k][qc], to_t<T>(lam));
-          if (a.ahat_out) ((T*)a.ahat_out)[ij] = to_t<T>(ah);
+          if (a.ahat_out && f.uk[k][qc] >= 0) ((T*)a.ahat_out)[(size_t)f.rc[q] * nd.uld + f.uk[k][qc]] = to_t<T>(ah);
           rs[q] += (double)lam * (double)f.bj[k][qc] + (double)konst;
         }
       }
@@ -373,18 +421,23 @@ struct BoundEpi {
 // ------------------------------------------------------------------ a_hat only
 // a_hat = GEMM + acc_in + gamma^T G recomputed for the adjoint instead of
 // stored by the bound pass: the same sum as BoundEpi forms, written to
-// a.ahat_out (operand type T); nothing else is read or written.
+// a.ahat_out (operand type T, unstable neurons only); nothing else is read or
+// written.
 template <typename T>
 struct AhatEpi {
   BoundEpiArgs a;
-  static constexpr bool kColPre = false;
+  static constexpr bool kColPre = true;
+  __device__ inline const NodeDev& col_node() const { return a.nd; }
+  __device__ inline const CutCol& col_cuts() const { return a.cc; }
   template <int R, int TN, bool PE> struct Frag {
     int rc[R];
-    bool ev[TN][R];
+    bool ev[TN][R];      // element valid and unstable
     float aoff[TN][R];
+    int uk[TN][R];
   };
   template <int R, int TN, bool PE>
-  __device__ inline void load(Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc, int M, int N) const {
+  __device__ inline void load(Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc, int M, int N,
+                              const ColPre<TN>* pre = nullptr) const {
     const RowParams& rp = a.rp;
     int rr[R];
     bool rv[R];
@@ -397,13 +450,14 @@ struct AhatEpi {
       for (int q = 0; q < R; ++q) {
         jv[q] = lc.j[k][GCP_QC(q)] < N;
         jq[q] = jv[q] ? lc.j[k][GCP_QC(q)] : 0;
-        f.ev[k][q] = jv[q] && rv[q];
+        f.uk[k][q] = kind_rank((!PE && pre) ? pre->kind[k] : a.nd.kind[jq[q]]) - a.nd.rank0;
+        f.ev[k][q] = jv[q] && rv[q] && f.uk[k][q] >= 0;
       }
       float sG[R], sH[R], sQ[R];
-      gather_cuts<R, PE>(a.cc, rp.gammaT, rp.mp, jq, jv, rr, sG, sH, sQ);
+      gather_cuts<R, PE>(a.cc, rp.gammaT, rp.mp, jq, jv, rr, sG, sH, sQ, (!PE && pre) ? &pre->rng[k] : nullptr);
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        const float pre = a.acc_in ? a.acc_in[(size_t)f.rc[q] * a.nd.ld + jq[GCP_QC(q)]] : 0.f;
+        const float pre = a.acc_in ? acc_at<T>(a.acc_in, a.acc_t, (size_t)f.rc[q] * a.nd.ld + jq[GCP_QC(q)]) : 0.f;
         f.aoff[k][q] = pre + sG[q];
       }
     }
@@ -416,7 +470,7 @@ struct AhatEpi {
 #pragma unroll
       for (int q = 0; q < R; ++q)
         if (f.ev[k][q])
-          ((T*)a.ahat_out)[(size_t)f.rc[q] * a.nd.ld + lc.j[k][GCP_QC(q)]] = to_t<T>(val[k][q] + f.aoff[k][q]);
+          ((T*)a.ahat_out)[(size_t)f.rc[q] * a.nd.uld + f.uk[k][q]] = to_t<T>(val[k][q] + f.aoff[k][q]);
   }
 };
 
@@ -500,7 +554,7 @@ struct AdjEpi {
     bool ev[TN][R];
     float lj[TN][PE ? R : 1], uj[TN][PE ? R : 1], iul[TN][PE ? R : 1], addj[TN][PE ? R : 1];
     int rk[TN][R];
-    float ah[TN][R];     // stored a_hat
+    float ah[TN][R];     // stored a_hat (of an unstable neuron)
     float pre[TN][R];    // acc_in
     float sQ[TN][R];
     float al[TN][R], ma[TN][R], va[TN][R];
@@ -542,8 +596,11 @@ struct AdjEpi {
 #pragma unroll
       for (int q = 0; q < R; ++q) {
         const int j = jq[k][GCP_QC(q)];
-        f.ah[k][q] = from_t<T>(((const T*)a.ahat)[(size_t)f.rc[q] * nd.ld + j]);
-        f.pre[k][q] = a.acc_in ? a.acc_in[(size_t)f.rc[q] * nd.ld + j] : 0.f;
+        // a stable neuron has no a_hat (and its class never uses it): column 0
+        // stands in, so that the load needs no branch
+        const int uk = max(kind_rank(kv[k][GCP_QC(q)]) - nd.rank0, 0);
+        f.ah[k][q] = a.ahat ? from_t<T>(((const T*)a.ahat)[(size_t)f.rc[q] * nd.uld + uk]) : 0.f;
+        f.pre[k][q] = a.acc_in ? acc_at<T>(a.acc_in, a.acc_t, (size_t)f.rc[q] * nd.ld + j) : 0.f;
       }
     }
 #pragma unroll
@@ -575,6 +632,57 @@ struct AdjEpi {
                          f.has_rgc ? &f.rgc[k] : nullptr);
     }
   }
+  // derivatives of one element of class c at dL = d/d Lambda and a_hat = x:
+  // d/d a_hat, d/d (gamma^T Q), d/d alpha, d/d rho
+  __device__ static inline void derive(int c, float dL, float x, float sq, float al, float lj, float uj, float iul, float rho,
+                                       float& dA, float& dS, float& gA, float& gR) {
+    gA = 0.f;
+    gR = 0.f;
+    if (c == ACTIVE) {
+      dA = dL; dS = 1.f;
+    } else if (c == INACTIVE) {
+      dA = 0.f; dS = 0.f;
+    } else {
+      const float n = fmaxf(-x, 0.f), p = fmaxf(x, 0.f);
+      const float pos = x > 0.f ? 1.f : 0.f, neg = x < 0.f ? 1.f : 0.f;
+      float dLda, dhda, dLds, dhds;
+      if constexpr (PI) {
+        // Lambda = alpha p - rho n + t,  h = l rho n - [w n - s]_+,  w = u - (u - l) rho
+        const float w = uj - (uj - lj) * rho;
+        const float ind = w * n - sq > 0.f ? 1.f : 0.f;
+        dLda = al * pos + rho * neg;
+        dhda = neg * (ind * w - lj * rho);
+        dLds = 0.f;
+        dhds = ind;
+        gR = n * (lj + ind * (uj - lj) - dL);
+      } else if (sq >= uj * n) { dLda = al * pos; dhda = 0.f; dLds = 0.f; dhds = 0.f; }
+      else if (sq <= lj * n) { dLda = al * pos + neg; dhda = 0.f; dLds = 0.f; dhds = 1.f; }
+      else {
+        dLda = al * pos + uj * iul * neg;
+        dhda = -lj * uj * iul * neg;
+        dLds = iul;
+        dhds = -lj * iul;
+      }
+      dA = dL * dLda + dhda;
+      dS = dL * dLds + dhds;
+      gA = dL * p;
+    }
+  }
+  // d/d beta of one split slot: the Adam step in place, or the gradient out
+  __device__ inline void beta_grad(size_t ib, float gB) const {
+    if (a.adam.enabled) {
+      const GCP_CONSTANT_AS float* ac = cst(a.adam.consts);
+      const float b1 = a.adam.b1, b2 = a.adam.b2;
+      const float mm = b1 * a.m_beta[ib] + (1.f - b1) * gB;
+      const float vv = b2 * a.v_beta[ib] + (1.f - b2) * gB * gB;
+      a.m_beta[ib] = mm;
+      a.v_beta[ib] = vv;
+      const float stp = adam_step(ac[1], mm, vv, ac[2], ac[3], a.adam.eps);
+      a.beta_rw[ib] = fmaxf(a.beta_rw[ib] + stp, 0.f);
+    } else {
+      a.d_beta[ib] = gB;
+    }
+  }
   template <int R, int TN, bool PE>
   __device__ inline void apply(const Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc,
                                const float (&val)[TN][R], double (&rs)[R], int M, int N) const {
@@ -586,9 +694,10 @@ struct AdjEpi {
                                   const float (&val)[TN][R], double (&rs)[R], int M, int N, const Sink& da_sink) const {
     const NodeDev& nd = a.nd;
     const RowParams& rp = a.rp;
-    float lr_a = 0.f, lr_m = 0.f, ibc1 = 1.f, ibc2 = 1.f;
+    float lr_a = 0.f, ibc1 = 1.f, ibc2 = 1.f;
     if (a.adam.enabled) {
-      lr_a = a.adam.consts[0]; lr_m = a.adam.consts[1]; ibc1 = a.adam.consts[2]; ibc2 = a.adam.consts[3];
+      const GCP_CONSTANT_AS float* ac = cst(a.adam.consts);
+      lr_a = ac[0]; ibc1 = ac[2]; ibc2 = ac[3];
     }
     const float b1 = a.adam.b1, b2 = a.adam.b2, aeps = a.adam.eps;
     // dense lanes hold four consecutive rows per group: their cut-gradient
@@ -601,38 +710,10 @@ struct AdjEpi {
       for (int q = 0; q < R; ++q) {
         const int qc = GCP_QC(q);
         const float dL = a.gemm_scale * val[k][q] + f.addj[k][qc] + f.pre[k][q];
-        float dA, dS, gA = 0.f, gR = 0.f;
+        float dA, dS, gA, gR;
         const int c = f.c[k][q];
-        if (c == ACTIVE) {
-          dA = dL; dS = 1.f;
-        } else if (c == INACTIVE) {
-          dA = 0.f; dS = 0.f;
-        } else {
-          const float x = f.ah[k][q], n = fmaxf(-x, 0.f), p = fmaxf(x, 0.f), sq = f.sQ[k][q];
-          const float pos = x > 0.f ? 1.f : 0.f, neg = x < 0.f ? 1.f : 0.f;
-          const float uj = f.uj[k][qc], lj = f.lj[k][qc], iul = f.iul[k][qc], al = f.al[k][q];
-          float dLda, dhda, dLds, dhds;
-          if constexpr (PI) {
-            // Lambda = alpha p - rho n + t,  h = l rho n - [w n - s]_+,  w = u - (u - l) rho
-            const float rho = f.rh[k][q], w = uj - (uj - lj) * rho;
-            const float ind = w * n - sq > 0.f ? 1.f : 0.f;
-            dLda = al * pos + rho * neg;
-            dhda = neg * (ind * w - lj * rho);
-            dLds = 0.f;
-            dhds = ind;
-            gR = n * (lj + ind * (uj - lj) - dL);
-          } else if (sq >= uj * n) { dLda = al * pos; dhda = 0.f; dLds = 0.f; dhds = 0.f; }
-          else if (sq <= lj * n) { dLda = al * pos + neg; dhda = 0.f; dLds = 0.f; dhds = 1.f; }
-          else {
-            dLda = al * pos + uj * iul * neg;
-            dhda = -lj * uj * iul * neg;
-            dLds = iul;
-            dhds = -lj * iul;
-          }
-          dA = dL * dLda + dhda;
-          dS = dL * dLds + dhds;
-          gA = dL * p;
-        }
+        derive(c, dL, f.ah[k][q], f.sQ[k][q], f.al[k][q], f.lj[k][qc], f.uj[k][qc], f.iul[k][qc],
+               PI ? f.rh[k][PI ? q : 0] : 0.f, dA, dS, gA, gR);
         cA[q] = dA; cL[q] = dL; cS[q] = dS;
         if (!f.ev[k][q]) continue;
         const int j = lc.j[k][qc];
@@ -669,18 +750,7 @@ struct AdjEpi {
         }
         const int sl = f.slot[k][q];
         if (sl >= 0) {
-          const size_t ib = (size_t)f.rc[q] * rp.K + sl;
-          const float gB = (c == ACTIVE) ? -dL : dL;
-          if (a.adam.enabled) {
-            const float mm = b1 * a.m_beta[ib] + (1.f - b1) * gB;
-            const float vv = b2 * a.v_beta[ib] + (1.f - b2) * gB * gB;
-            a.m_beta[ib] = mm;
-            a.v_beta[ib] = vv;
-            const float stp = adam_step(lr_m, mm, vv, ibc1, ibc2, aeps);
-            a.beta_rw[ib] = fmaxf(a.beta_rw[ib] + stp, 0.f);
-          } else {
-            a.d_beta[ib] = gB;
-          }
+          beta_grad((size_t)f.rc[q] * rp.K + sl, (c == ACTIVE) ? -dL : dL);
         }
       }
       if constexpr (kVecContrib) {

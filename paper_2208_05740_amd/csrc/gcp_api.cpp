@@ -223,6 +223,8 @@ struct EdgeH {
   DBuf WT16f;    // conv: WT16's values as fp32 (read by the direct transposed conv in bf16 mode)
   DBuf Wraw;     // dense [d_dst][d_src] unpadded fp32 (for c-hat and W x0); conv: [co][ci][kh][kw]
   int ldk_f = 0, ldk_t = 0;   // conv: padded K of W32/W16 (adjoint) and WT32/WT16 (bound)
+  ConvPlan plan[2];           // conv: conv_plan(cg, trans)
+  DBuf uns[2], uns_off[2];    // conv: unstable neurons band by band (ConvArgs::uns), [0] adjoint on dst, [1] bound on src
 };
 
 struct NodeH {
@@ -232,6 +234,7 @@ struct NodeH {
   std::vector<int> consumers;     // edges whose src is this node
   DBuf bias, rec, kind;
   std::vector<int32_t> rank_h;    // host copy of rank
+  std::vector<int32_t> kind_h;    // host copy of kind
   std::vector<double> l_h, u_h;   // host copies of the root bounds (as given)
   // outward rounding: Z = max(|l|, |u|) and Y = the largest |x_hat| the
   // relaxation faces (0 inactive, u active, max(-l, u) unstable), both from
@@ -239,7 +242,10 @@ struct NodeH {
   std::vector<double> z_h, y_h;
   DBuf slack_w;                   // fp64 [5][ld]: the node's outward-rounding weights
   int n_unst = 0, rank0 = 0;
-  NodeDev dev() const { return NodeDev{size, ld, rec.as<float4>(), kind.as<int32_t>()}; }
+  int uld() const { return (n_unst + 15) / 16 * 16; }   // row pitch of the node's a_hat
+  NodeDev dev() const {
+    return NodeDev{size, ld, rec.as<float4>(), kind.as<int32_t>(), bias.as<float>(), uld(), rank0};
+  }
 };
 
 }  // namespace
@@ -296,14 +302,18 @@ struct gcp_cuts {
   DBuf row_ptr;     // [N + 1] over merged entries in cut-major order
   DBuf d;           // fp64 [N]
   struct Col {
-    DBuf rng, ent, pos;
+    DBuf rng, ent, pos, stable;
     bool any = false;
     CutCol dev() const {
-      if (!any) return CutCol{nullptr, nullptr, nullptr};
-      return CutCol{rng.as<int2>(), ent.as<float4>(), pos.as<int32_t>()};
+      if (!any) return CutCol{nullptr, nullptr, nullptr, nullptr};
+      return CutCol{rng.as<int2>(), ent.as<float4>(), pos.as<int32_t>(), stable.as<uint8_t>()};
     }
   };
   std::vector<Col> cols;   // per node; index n_nodes is the network input
+  // per conv edge and direction (as EdgeH::uns): neurons without an alpha
+  // that have entries, band by band (ConvArgs::cut); null buffers if none
+  struct EdgeList { DBuf ent[2], off[2]; };
+  std::map<int, EdgeList> edge_lists;
   std::vector<int> nnz_node;   // merged entries per node (same indexing)
   // outward rounding: fp64 [3][N] = sum |coef| range over a cut's node
   // entries (range Z for H and G, 2 for Q), sum |coef| over its input
@@ -364,6 +374,25 @@ std::vector<float> bf16_as_f32(const std::vector<uint16_t>& v) {
     std::memcpy(&o[i], &b, 4);
   }
   return o;
+}
+
+// The neurons of `pick` (ascending) band by band of a conv launch's plan:
+// {neuron, kind} entries and the first entry of each band.
+void upload_band_list(const ConvPlan& P, const std::vector<int32_t>& pick, const std::vector<int32_t>* kind,
+                      DBuf& ent, DBuf& off) {
+  std::vector<std::vector<int2>> by(P.n_bands);
+  for (int32_t j : pick) {
+    const int y = (j / P.We) % P.He;
+    by[y / P.BH].push_back(make_int2(j, kind ? (*kind)[j] : 0));
+  }
+  std::vector<int2> e;
+  std::vector<int32_t> o(1, 0);
+  for (auto& b : by) {
+    e.insert(e.end(), b.begin(), b.end());
+    o.push_back((int32_t)e.size());
+  }
+  ent.upload(e);
+  off.upload(o);
 }
 
 int node_size_of(const gcp_net* net, int src) { return src < 0 ? net->in_size : net->nodes[src].size; }
@@ -487,6 +516,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
     }
     n.rec.upload(rec);
     n.kind.upload(kind);
+    n.kind_h = kind;
     for (int e = 0; e < nd.n_edges; ++e) {
       const gcp_edge_desc& ed = nd.edges[e];
       if (ed.src < -1 || ed.src >= i) fail(GCP_EINVAL, "edge source must be an earlier node or the input");
@@ -538,9 +568,13 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
         std::vector<float> fw((size_t)n.c * kf), ft((size_t)nph * ci * kt);
         conv_pack_weights(E->cg, 0, raw.data(), fw.data());
         conv_pack_weights(E->cg, 1, raw.data(), ft.data());
-        const ConvPlan pf = conv_plan(E->cg, 0), pt = conv_plan(E->cg, 1);
-        if (pf.rows_max * pf.Wp * pf.Kch * 4 > 48 * 1024 || pt.rows_max * pt.Wp * pt.Kch * 4 > 48 * 1024)
+        long slab_f = 0, slab_t = 0;
+        conv_accepted(E->cg, 0, &slab_f);
+        conv_accepted(E->cg, 1, &slab_t);
+        if (slab_f > 48 * 1024 || slab_t > 48 * 1024)
           fail(GCP_EUNSUPPORTED, "conv rows too wide for an LDS slab");
+        E->plan[0] = conv_plan(E->cg, 0);
+        E->plan[1] = conv_plan(E->cg, 1);
         E->ldk_f = kf;
         E->ldk_t = kt;
         E->W32.upload(fw); E->W16.upload(to_bf16(fw));
@@ -564,6 +598,17 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
             }
         e_wy.push_back(std::move(wy));
         e_terms.push_back((double)n.c * ed.kh * ed.kw);
+        auto unstable_of = [](const NodeH& t) {
+          std::vector<int32_t> u;
+          for (int j = 0; j < t.size; ++j)
+            if (t.rank_h[j] >= 0) u.push_back(j);
+          return u;
+        };
+        if (n.relu) upload_band_list(E->plan[0], unstable_of(n), &n.kind_h, E->uns[0], E->uns_off[0]);
+        if (ed.src >= 0) {
+          const NodeH& sn = net->nodes[ed.src];
+          upload_band_list(E->plan[1], unstable_of(sn), &sn.kind_h, E->uns[1], E->uns_off[1]);
+        }
       } else if (ed.kind == GCP_EDGE_IDENTITY) {
         if (E->d_src != E->d_dst) fail(GCP_EINVAL, "identity edge between different sizes");
         if (ed.src < 0) e_wy.emplace_back(E->d_dst, 1.0);
@@ -685,9 +730,9 @@ bool conv_direct_enabled() {
   const char* e = std::getenv("GCP_CONV_DIRECT");
   return !(e && e[0] == '0');
 }
-Cands conc_conv_cands(const ConvGeom& g) {
+Cands conc_conv_cands(const ConvGeom& g, const ConvPlan& plan) {
   Cands c = conv_cands();
-  if (conv_direct_enabled() && conv_direct_ok(g, EPI_CONC)) {
+  if (conv_direct_enabled() && conv_direct_ok(g, plan, EPI_CONC)) {
     c.list.push_back(kConvDirectCfg);
     c.fallback = kConvDirectCfg;
   }
@@ -915,6 +960,23 @@ extern "C" int gcp_cuts_create(const gcp_net* net, int32_t n_cuts, int64_t nnz, 
     for (int j = 0; j < sz; ++j) rg[j] = make_int2(cp[j], cp[j + 1]);
     col.rng.upload(rg); col.ent.upload(en); col.pos.upload(cpos);
     col.any = true;
+    // neurons without an alpha (root-stable, or the input's) that have entries
+    std::vector<int32_t> other;
+    std::vector<uint8_t> flag(sz, 0);
+    for (int j = 0; j < sz; ++j)
+      if (rg[j].x < rg[j].y && (nd < 0 || net->nodes[nd].rank_h[j] < 0)) {
+        other.push_back(j);
+        flag[j] = 1;
+      }
+    if (other.empty()) continue;
+    col.stable.upload(flag);
+    for (int e = 0; e < (int)net->edges.size(); ++e) {
+      const EdgeH& E = *net->edges[e];
+      if (E.kind != GCP_EDGE_CONV) continue;
+      const std::vector<int32_t>* kind = nd < 0 ? nullptr : &net->nodes[nd].kind_h;
+      if (E.dst == nd) upload_band_list(E.plan[0], other, kind, C->edge_lists[e].ent[0], C->edge_lists[e].off[0]);
+      if (E.src == nd) upload_band_list(E.plan[1], other, kind, C->edge_lists[e].ent[1], C->edge_lists[e].off[1]);
+    }
   }
   *out = C.release();
   g_err.clear();
@@ -1309,7 +1371,7 @@ void ensure_ws(Call& c) {
 }
 
 CutCol cut_col(const Call& c, int node) {
-  if (!c.cuts) return CutCol{nullptr, nullptr, nullptr};
+  if (!c.cuts) return CutCol{nullptr, nullptr, nullptr, nullptr};
   int idx = node < 0 ? (int)c.net->nodes.size() : node;
   return c.cuts->cols[idx].dev();
 }
@@ -1375,6 +1437,20 @@ void no_record(const Call& c, const char* what) {
   if (c.rec) fail(GCP_EUNSUPPORTED, std::string("batched optimisation supports dense edges only (") + what + ")");
 }
 
+// the plan and the band lists of a conv launch through edge eid (see ConvArgs)
+void set_plan(const Call& c, int eid, ConvArgs& ca) {
+  const EdgeH& E = *c.net->edges[eid];
+  const int t = ca.trans;
+  ca.plan = &E.plan[t];
+  ca.uns = E.uns[t].as<int2>();
+  ca.uns_off = E.uns_off[t].as<int32_t>();
+  if (!c.cuts) return;
+  auto it = c.cuts->edge_lists.find(eid);
+  if (it == c.cuts->edge_lists.end()) return;
+  ca.cut = it->second.ent[t].as<int2>();
+  ca.cut_off = it->second.off[t].as<int32_t>();
+}
+
 const void* wt_bound(const EdgeH& E, int bf16) { return bf16 ? E.WT16.p : E.WT32.p; }
 const void* w_adj(const EdgeH& E, int bf16) { return bf16 ? E.W16.p : E.W32.p; }
 
@@ -1390,10 +1466,10 @@ struct BoundPass {
   bool dry;           // count partial slots only
   int slot = 0;
   std::vector<int> pushes_left;   // per node (index n_nodes: input)
-  // Per node: the fp32 Lambda that stands in for its accumulation buffer when
-  // an identity edge is the first of exactly two pushes (the copy into the
-  // buffer would be exact), or null.
-  std::vector<const float*> acc_alias;
+  // Per node: the Lambda (operand type) that stands in for its accumulation
+  // buffer when an identity edge is the first of exactly two pushes (the copy
+  // into the buffer would be exact), or null.
+  std::vector<const void*> acc_alias;
 
   BoundPass(Call& cc, int b, bool k, bool wc, bool d) : c(cc), bf16(b), keep_ahat(k), want_contrib(wc), dry(d) {}
 
@@ -1405,7 +1481,8 @@ struct BoundPass {
     a.nd = c.net->nodes[p].dev();
     a.cc = cut_col(c, p);
     a.rp = c.rp;
-    a.acc_in = has_acc ? (acc_alias[p] ? acc_alias[p] : ws.acc[p]->as<float>()) : nullptr;
+    a.acc_in = has_acc ? (acc_alias[p] ? acc_alias[p] : ws.acc[p]->p) : nullptr;
+    a.acc_t = acc_alias[p] != nullptr;
     a.lam_out = ws.lam[p]->p;
     const bool rec = !c.recompute.empty() && c.recompute[p];
     a.ahat_out = (keep_ahat && !rec) ? ws.ahat[p]->p : nullptr;
@@ -1579,6 +1656,7 @@ struct BoundPass {
       ca.Bt = bf16 ? E.WT16.p : E.WT32.p; ca.ldb = E.ldk_t;
       ca.Btf = (const float*)(bf16 ? E.WT16f.p : E.WT32.p);
       ca.mp = c.rp.mp; ca.partial = nullptr;
+      set_plan(c, eid, ca);
       const double M = c.M, esz = bf16 ? 2 : 4;
       // every multiply-add of the forward conv appears once in its transpose
       const double flops = 2.0 * M * cg.ho * cg.wo * cg.ci * cg.co * cg.kh * cg.kw;
@@ -1598,7 +1676,7 @@ struct BoundPass {
         }
         return;
       }
-      const int nslot = conv_slots(cg, 1);
+      const int nslot = E.plan[1].n_bands;   // row-partial slots: one per band
       if (p >= 0) {
         BoundEpiArgs a = bound_args(p, has_acc);
         if (!dry) {
@@ -1623,7 +1701,7 @@ struct BoundPass {
         a.contrib = want_contrib ? ws.contrib.as<float>() : nullptr;
         a.nnz_e = c.nnz;
         if (!dry) {
-          int cfg = choose_cfg("convT", EPI_CONC, bf16, 0, c.M, d_src, dn.size, c.st, conc_conv_cands(cg),
+          int cfg = choose_cfg("convT", EPI_CONC, bf16, 0, c.M, d_src, dn.size, c.st, conc_conv_cands(cg, E.plan[1]),
                                [&](int cf) { return launch_conv(bf16, cf, EPI_CONC, ca, &a, c.st); });
           ConvArgs cr = ca;
           cr.partial = ws.partial.as<double>(); cr.slot0 = slot;
@@ -1641,8 +1719,8 @@ struct BoundPass {
       no_record(c, "identity");
       if (p < 0) fail(GCP_EUNSUPPORTED, "identity edge from the network input");
       if (!last) {
-        if (!bf16 && first && total == 2 && dn.ld == ld_src) {
-          acc_alias[p] = ws.lam[E.dst]->as<float>();   // the last push reads it in place of the buffer
+        if (first && total == 2 && dn.ld == ld_src) {
+          acc_alias[p] = ws.lam[E.dst]->p;   // the last push reads it in place of the buffer
           return;
         }
         if (!dry)
@@ -1742,6 +1820,7 @@ struct AdjPass {
       ca.Bt = bf16 ? E.WT16.p : E.WT32.p; ca.ldb = E.ldk_t;
       ca.Btf = (const float*)(bf16 ? E.WT16f.p : E.WT32.p);
       ca.mp = c.rp.mp; ca.partial = nullptr;
+      set_plan(c, n.consumers[0], ca);
       const ConvGeom& cg = E.cg;
       const int cfg = choose_cfg("convT", EPI_BOUND, bf16, 0, c.M, E.d_src, dn.size, c.st, conv_cands(),
                                  [&](int cf) { return launch_conv(bf16, cf, EPI_AHAT, ca, &a, c.st); });
@@ -1765,10 +1844,10 @@ struct AdjPass {
       if (net->edges[eid]->kind != GCP_EDGE_IDENTITY) order.push_back(eid);
     float* accbuf = ws.acc[i]->p ? ws.acc[i]->as<float>() : nullptr;
     // what the fused epilogue reads as the accumulated dLambda: the buffer, or,
-    // when an identity edge from an fp32 d a_hat is the first of exactly two
-    // edges and the other is a GEMM edge (its copy into the buffer would be
-    // exact), that d a_hat itself
-    const float* acc_rd = accbuf;
+    // when an identity edge from a d a_hat is the first of exactly two edges
+    // and the other is a GEMM edge (its copy into the buffer would be exact),
+    // that d a_hat itself
+    const void* acc_rd = accbuf;
     // the node's adjoint epilogue runs fused with its last GEMM, or
     // elementwise after all edges when the last edge is an identity
     const bool pi = c.rp.rho != nullptr;
@@ -1832,6 +1911,7 @@ struct AdjPass {
         ca.X = A; ca.ldx = lda; ca.x_is_sign = sign;
         ca.Bt = bf16 ? E.W16.p : E.W32.p; ca.ldb = E.ldk_f;
         ca.mp = c.rp.mp; ca.partial = nullptr;
+        set_plan(c, order[q], ca);
         const int HW = E.cg.ho * E.cg.wo;
         const double flops = 2.0 * M * HW * E.cg.co * E.cg.ci * E.cg.kh * E.cg.kw;
         const double wbytes = (double)E.cg.co * E.ldk_f * esz;
@@ -1862,8 +1942,8 @@ struct AdjPass {
         }
       } else {   // identity: accumulate; the node's relaxation runs after the last edge
         no_record(c, "identity");
-        if (!bf16 && !sign && first && !last && fused_last && order.size() == 2 && lda == n.ld) {
-          acc_rd = (const float*)A;
+        if (!sign && first && !last && fused_last && order.size() == 2 && lda == n.ld) {
+          acc_rd = A;
           continue;
         }
         check(launch_identity_acc(bf16, c.M, n.size, A, lda, sign, scale, first ? nullptr : accbuf, accbuf, n.ld,
@@ -1877,7 +1957,7 @@ struct AdjPass {
     }
   }
 
-  AdjEpiArgs epi(int i, const float* acc_in, float scale) {
+  AdjEpiArgs epi(int i, const void* acc_in, float scale) {
     gcp_net* net = c.net;
     auto& ws = *c.ws;
     const NodeH& n = net->nodes[i];
@@ -1886,6 +1966,7 @@ struct AdjPass {
     a.cc = cut_col(c, i);
     a.rp = c.rp;
     a.acc_in = acc_in;
+    a.acc_t = acc_in != ws.acc[i]->p;   // a d a_hat read in place of the buffer
     a.gemm_scale = scale;
     a.add_vec = add_vec_of(c, i);
     a.ahat = c.recompute.empty() || !c.recompute[i] ? ws.ahat[i]->p : ws.ahat_tmp.p;
@@ -1957,7 +2038,7 @@ void plan_ahat(Call& c, int32_t mode) {
   const int nn = (int)net->nodes.size();
   size_t stored = 0;
   for (int i = 0; i < nn; ++i)
-    if (net->nodes[i].relu) stored += (size_t)c.M * net->nodes[i].ld * 4;
+    if (net->nodes[i].relu) stored += (size_t)c.M * net->nodes[i].uld() * 4;
   const char* e = std::getenv("GCP_AHAT_BUDGET_MB");
   double budget = 8192.0 * 1048576.0;
   if (e && *e) {
@@ -1976,7 +2057,7 @@ void plan_ahat(Call& c, int32_t mode) {
   for (int i = 0; i < nn; ++i) {
     const NodeH& n = net->nodes[i];
     if (!n.relu) continue;
-    const size_t bytes = (size_t)c.M * n.ld * 4;
+    const size_t bytes = (size_t)c.M * n.uld() * 4;
     if (want && ahat_recomputable(net, i)) {
       c.recompute[i] = 1;
       tmp = std::max(tmp, bytes);
@@ -2136,7 +2217,7 @@ void carve_static(Call& c, gcp_net::WS& sws, int bf16, bool grads) {
     take(*sws.lam[i], elems * 4);
     take(*sws.acc[i], multi ? elems * 4 : 0);
     if (grads) {
-      take(*sws.ahat[i], n.relu ? elems * 4 : 0);
+      take(*sws.ahat[i], n.relu ? M * n.uld() * 4 : 0);
       take(*sws.dahat[i], elems * 4);
       take(*sws.addv[i], n.relu ? (size_t)n.ld * 4 : 0);
     }

@@ -18,6 +18,8 @@ struct NodeDev {
   // the reciprocal width for unstable neurons (else 0), the layer bias
   const float4* rec;
   const int32_t* kind;   // (rank + 1) * 4 + root class; rank = column in an alpha row, or -1
+  const float* bias;     // [size] (rec's fourth word, four neurons per load)
+  int uld, rank0;        // a_hat buffers: row pitch (unstable neurons, rounded up to 16) and the first rank
 };
 __host__ __device__ inline int kind_rank(int v) { return (v >> 2) - 1; }
 __host__ __device__ inline int kind_cls(int v) { return v & 3; }
@@ -31,6 +33,7 @@ struct CutCol {
   const int2* rng;         // [size], null if the node has no entries
   const float4* ent;
   const int32_t* pos;
+  const uint8_t* stable;   // [size] 1 where a neuron without an alpha has entries; null if none has
 };
 
 // Per-row parameters of one call.  Row-indexed internal buffers use the
@@ -61,9 +64,12 @@ enum EpiKind { EPI_STORE = 0, EPI_BOUND = 1, EPI_CONC = 2, EPI_ADJ = 3, EPI_AHAT
 
 struct BoundEpiArgs {       // Theorem 3.1 relaxation of one ReLU node
   NodeDev nd; CutCol cc; RowParams rp;
-  const float* acc_in;      // optional extra pre-activation [M][ld] (fp32)
+  const void* acc_in;       // optional extra pre-activation [M][ld], fp32 or (acc_t) the operand type
+  int acc_t;
   void* lam_out;            // [M][ld] in the GEMM operand type
-  void* ahat_out;           // optional [M][ld] in the GEMM operand type (kept for the adjoint)
+  // optional [M][nd.uld] in the GEMM operand type, kept for the adjoint: a_hat
+  // of the node's unstable neurons in rank order (the adjoint reads no other)
+  void* ahat_out;
 };
 // EPI_AHAT (recomputing a_hat for the adjoint) takes BoundEpiArgs and writes
 // only ahat_out.
@@ -77,10 +83,11 @@ struct ConcEpiArgs {        // concretisation over the input box
 };
 struct AdjEpiArgs {         // adjoint of one ReLU node's relaxation
   NodeDev nd; CutCol cc; RowParams rp;
-  const float* acc_in;      // optional extra dLambda [M][ld]
+  const void* acc_in;       // optional extra dLambda [M][ld], fp32 or (acc_t) the operand type
+  int acc_t;
   float gemm_scale;         // multiplies the GEMM result (-eps for the input edge)
   const float* add_vec;     // [size] added to dLambda (bias, or W x0 + b)
-  const void* ahat;         // [M][ld] stored pre-activation coefficients (operand type)
+  const void* ahat;         // [M][nd.uld] stored pre-activation coefficients (operand type)
   void* dahat_out;          // [M][ld] operand type, null if no consumer needs it
   float* contrib; int nnz_e;           // [nnz_e][mp]
   float* d_alpha; float* d_beta;      // raw gradient outputs (adam disabled)
@@ -163,6 +170,7 @@ struct ConvGeom { int ci, hi, wi, co, ho, wo, kh, kw, stride, pad; };
 // type, or int8 signs) -> epilogue over the node's (co, ho, wo);
 // Bt = W [co][ldb], entry (c, ky, kx), K = ci*kh*kw padded to ldb.
 // ldb is a multiple of 32 in both.
+struct ConvPlan;
 struct ConvArgs {
   int M;                  // batch rows
   ConvGeom cg;
@@ -171,33 +179,42 @@ struct ConvArgs {
   const void* Bt; int ldb;
   const float* Btf;       // transposed direction: Bt's values as fp32 (bf16-rounded in bf16 mode), for the direct kernel
   double* partial; int mp; int slot0;
+  // the epilogue-side neurons that need the full epilogue, {neuron, kind}
+  // band by band (entries off[b] .. off[b + 1] - 1 belong to band b): the
+  // unstable ones, and in a second list the other ones with cut entries
+  const int2* uns; const int32_t* uns_off;
+  const int2* cut; const int32_t* cut_off;
+  const ConvPlan* plan;   // host: conv_plan(cg, trans)
 };
 // Work split of one conv launch: the epilogue-side rows form bands of BH
-// rows; one workgroup stages the source rows a band reads (with a zero halo)
-// in LDS for one batch row, produces every output of that band into a second
-// LDS buffer and runs the epilogue over it.
+// rows; one workgroup takes four batch rows and one band: it stages the
+// source rows the band reads (with a zero halo) in LDS, produces every
+// output of the band and runs the epilogue over it.
 struct ConvPlan {
   int He, We, Nch, Kch, hs, ws;   // epilogue side (He x We, Nch channels), source side (Kch x hs x ws)
   int s, p, A, Bn;                // stride, pad; taps per phase and dimension
-  int n_phase, Kreal, KP;         // phases; GEMM K per phase, padded
+  int n_phase, Kreal, KP;         // phases; GEMM K per phase, padded to a multiple of 32
   int BH, n_bands;
   int rows_max, xl, Wp, CHS;      // LDS slab: rows per channel, left halo, pitch, channel stride
   int OS;                         // LDS result band: channel stride
   int MT;                         // most 16-row GEMM tiles in one band (phases padded to 16 rows)
+  int rb;                         // batch rows in the slab at once: 4, or 1 where four do not fit
 };
+// Whether a launch takes the conv: a slab of one batch row and the results of
+// four within 64 KB; slab_bytes (optional) gets that slab's size.
+bool conv_accepted(const ConvGeom& g, int trans, long* slab_bytes = nullptr);
 ConvPlan conv_plan(const ConvGeom& g, int trans);
 // conv weights laid out as the kernels read them (Bt above); raw is [co][ci][kh][kw]
 int conv_ldb(const ConvGeom& g, int trans);
 void conv_pack_weights(const ConvGeom& g, int trans, const float* raw, float* out);
+// cfg >= conv_num_configs() (a tile file written when there were more shapes) runs as 8 waves x 1 column tile
 hipError_t launch_conv(int bf16, int cfg, EpiKind kind, const ConvArgs& c, const void* epi, hipStream_t st);
 int conv_num_configs();
 // launch_conv's cfg for the direct (VALU) transposed convolution, and whether
 // it applies: concretisation over a source of at most four channels, taps
 // per phase 2x2 at stride 2 or 3x3 at stride 1
 constexpr int kConvDirectCfg = 6;
-bool conv_direct_ok(const ConvGeom& g, EpiKind kind);
-// row-partial slots a conv launch owns: one per band
-inline int conv_slots(const ConvGeom& g, int trans) { return conv_plan(g, trans).n_bands; }
+bool conv_direct_ok(const ConvGeom& g, const ConvPlan& plan, EpiKind kind);
 
 hipError_t launch_chat(const double* C, int S, int d_out, const float* W, int d_in,
                        int kind, float* chat, int ld, hipStream_t st);

@@ -14,16 +14,6 @@ namespace gcp {
 // C[M][N] = A[M][K] * Bt[N][K]^T on MFMA, epilogue per element, row partial
 // sums reduced deterministically (lanes, then waves through LDS) into
 // partial[r][slot0 + blockIdx.x].
-// XCD-aware tile order: workgroups are dispatched round-robin over the 8
-// XCDs by linear id, so the ids an XCD receives map onto a contiguous run of
-// tiles (row panel major) and all column tiles of a row panel share that
-// XCD's L2 instead of fetching the A panel once per XCD.
-__device__ inline int xcd_tile(int id, int total) {
-  const int xcd = id % 8, kx = id / 8;
-  const int per = total / 8, rem = total % 8;
-  return xcd * per + (xcd < rem ? xcd : rem) + kx;
-}
-
 // LDS of one tile: the A and B stages (16-byte row padding) and the per-wave
 // row partials.
 template <typename T, int BM, int BN, int WN, int BK>
