@@ -33,6 +33,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 #else
 #define GCP_CONSTANT_AS
 #endif
+#if defined(__HIP_DEVICE_COMPILE__)
+#define GCP_GLOBAL_AS __attribute__((address_space(1)))
+#else
+#define GCP_GLOBAL_AS
+#endif
 template <typename T>
 __device__ inline const GCP_CONSTANT_AS T* cst(const T* p) {
   return (const GCP_CONSTANT_AS T*)p;
@@ -174,6 +179,146 @@ __device__ inline void col_prefetch(ColPre<TN>& p, const NodeDev& nd, const CutC
   }
 }
 
+// Operands of one 16x16 sub-tile of a wave (layer_tile in tiles.h) that are
+// fetched before the GEMM's K loop: the neuron's words, and the rank-addressed
+// values of the lane's four rows.
+struct SubPre {
+  int kind;
+  int2 rng;
+  float4 rec;
+  float addv;                         // adjoint: add_vec of the column
+  int8_t mask[4];                     // split mask
+  float al[4], ah[4], ma[4], va[4];   // alpha; in the adjoint a_hat and alpha's Adam moments
+};
+
+// A lane's place in a tile of rows m0 .. m0 + rows - 1 (wave-uniform): rows
+// m0 + rl .. + 3, those below rows exist, and column j, which exists if jv
+// (jc: j, or the last column).
+struct TileLane {
+  int m0, rows, rl, j, jc;
+  bool jv;
+  __device__ inline bool any() const { return jv && rl < rows; }
+};
+
+// The tile functions address global memory through buffer descriptors: one
+// per array and tile (wave-uniform, the tile's rows), 32-bit byte offsets per
+// lane.  A read past the descriptor's end gives 0 and a write there is
+// dropped, so ragged rows need no test, and a lane without an element (column
+// past the edge, no alpha) passes kNoElem: the accesses carry no branches and
+// the loads in flight stay countable.  With 64-bit addresses per access and
+// clamped rows the address arithmetic was a third of the epilogues' vector
+// instructions.
+constexpr uint32_t kNoElem = 0x80000000u;
+#if defined(__HIP_DEVICE_COMPILE__)
+struct RowWin {
+  __amdgpu_buffer_rsrc_t r;
+};
+__device__ inline RowWin row_win(const void* base, size_t first, int rows, uint32_t pitch) {
+  return RowWin{__builtin_amdgcn_make_buffer_rsrc((char*)base + first * pitch, 0, base ? (int)(rows * pitch) : 0, 0x00027000)};
+}
+template <typename V> __device__ inline V win_ld(const RowWin& w, uint32_t off) {
+  if constexpr (sizeof(V) == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(w.r, off, 0, 0));
+  else if constexpr (sizeof(V) == 2) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b16(w.r, off, 0, 0));
+  else return (V)__builtin_amdgcn_raw_buffer_load_b8(w.r, off, 0, 0);
+}
+template <typename V> __device__ inline void win_st(const RowWin& w, uint32_t off, V v) {
+  if constexpr (sizeof(V) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), w.r, off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), w.r, off, 0, 0);
+}
+#else
+struct RowWin {};
+__device__ inline RowWin row_win(const void*, size_t, int, uint32_t) { return RowWin{}; }
+template <typename V> __device__ inline V win_ld(const RowWin&, uint32_t) { return V{}; }
+template <typename V> __device__ inline void win_st(const RowWin&, uint32_t, V) {}
+#endif
+template <typename V>
+__device__ inline V ld_at(const void* base, uint32_t off) {
+  return *(const GCP_GLOBAL_AS V*)((const GCP_GLOBAL_AS char*)base + off);
+}
+__device__ inline int div_rows(int r, int S, double inv_S);
+template <int R, bool PE>
+__device__ inline void gather_cuts(const CutCol& cc, const float* __restrict__ gammaT, int mp, const int (&jq)[R],
+                                   const bool (&jv)[R], const int (&rr)[R], float (&sG)[R], float (&sH)[R],
+                                   float (&sQ)[R], const int2* rg_pre);
+
+// offset of the lane's first row in an array of the given pitch (elements of
+// sz bytes; row q follows at + q pitch sz), column col, or kNoElem
+__device__ inline uint32_t lane_off(const TileLane& t, bool has, int pitch, int col, uint32_t sz) {
+  return has ? (uint32_t)(t.rl * pitch + col) * sz : kNoElem;
+}
+
+// What an epilogue of kPre fields (1: alpha; 3: also a_hat and the moments)
+// reads besides the product, for a lane whose neuron has the words p.kind.
+template <typename T, class Epi>
+__device__ __forceinline__ void fetch_pre(const Epi& epi, const TileLane& t, SubPre& p) {
+  const RowParams& rp = epi.a.rp;
+  const NodeDev& nd = epi.col_node();
+  const int rk = kind_rank(p.kind);
+  const bool has = t.jv && rk >= 0;
+  p.rec = ld_at<float4>(nd.rec, (uint32_t)t.jc * 16u);
+  const uint32_t pA = rp.n_I * 4u, oA = lane_off(t, has, rp.n_I, rk, 4);
+  const RowWin al = row_win(rp.alpha, t.m0, t.rows, pA);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) p.al[q] = win_ld<float>(al, oA + q * pA);
+  if constexpr (Epi::kPre == 3) {
+    p.addv = ld_at<float>(epi.a.add_vec, (uint32_t)t.jc * 4u);
+    const uint32_t pU = nd.uld * (uint32_t)sizeof(T), oU = lane_off(t, has, nd.uld, rk - nd.rank0, sizeof(T));
+    const bool adam = epi.a.adam.enabled;
+    const RowWin ah = row_win(epi.a.ahat, t.m0, t.rows, pU);
+    const RowWin ma = row_win(adam ? epi.a.m_alpha : nullptr, t.m0, t.rows, pA);
+    const RowWin va = row_win(adam ? epi.a.v_alpha : nullptr, t.m0, t.rows, pA);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      p.ah[q] = from_t<T>(win_ld<T>(ah, oU + q * pU));
+      p.ma[q] = win_ld<float>(ma, oA + q * pA);
+      p.va[q] = win_ld<float>(va, oA + q * pA);
+    }
+  }
+  // domains of the tile's rows, counted from that of row m0: rows are counted
+  // from its first row, at most S + 63; the float quotient of rows below 128
+  // by S < 64 is off an integer by 1 / 128 at least, far above its error
+  const int d0 = __builtin_amdgcn_readfirstlane(div_rows(t.m0, rp.S, rp.inv_S)), r0 = t.m0 - d0 * rp.S;
+  const float inv = (float)rp.inv_S;
+  auto dom = [&](int r) -> int { return rp.S >= 64 ? (r >= rp.S ? 1 : 0) : (int)(((float)r + 0.5f) * inv); };
+  const int nd_t = __builtin_amdgcn_readfirstlane(dom(r0 + t.rows - 1)) + 1;
+  const RowWin mk = row_win(rp.mask, d0, nd_t, rp.n_I);
+  const int dl = dom(r0 + t.rl);
+  int rem = r0 + t.rl - dl * rp.S;
+  uint32_t oM = has ? (uint32_t)(dl * rp.n_I + rk) : kNoElem;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    p.mask[q] = win_ld<int8_t>(mk, oM);
+    if (++rem == rp.S) { rem = 0; oM += rp.n_I; }
+  }
+}
+// gamma^T X at the lane's elements
+__device__ __forceinline__ void tile_cuts(const CutCol& cc, const RowParams& rp, const TileLane& t, const SubPre& p,
+                                          float (&sG)[4], float (&sH)[4], float (&sQ)[4]) {
+  const int jq[4] = {t.jc, t.jc, t.jc, t.jc}, rr[4] = {t.m0 + t.rl, 0, 0, 0};
+  const bool jv[4] = {t.any(), true, true, true};
+  gather_cuts<4, false>(cc, rp.gammaT, rp.mp, jq, jv, rr, sG, sH, sQ, &p.rng);
+}
+// effective class of row q
+__device__ inline int tile_cls(const SubPre& p, int q) {
+  const int m = (int)p.mask[q];
+  return m > 0 ? (int)ACTIVE : (m < 0 ? (int)INACTIVE : kind_cls(p.kind));
+}
+// accumulated values added to the product
+template <typename T>
+__device__ inline void tile_acc(const void* acc, int acc_t, const NodeDev& nd, const TileLane& t, float (&o)[4]) {
+  if (sizeof(T) == 2 && acc_t) {
+    const uint32_t pitch = nd.ld * 2u, off = lane_off(t, t.jv, nd.ld, t.j, 2);
+    const RowWin w = row_win(acc, t.m0, t.rows, pitch);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = from_t<bf16>(win_ld<bf16>(w, off + q * pitch));
+  } else {
+    const uint32_t pitch = nd.ld * 4u, off = lane_off(t, t.jv, nd.ld, t.j, 4);
+    const RowWin w = row_win(acc, t.m0, t.rows, pitch);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = win_ld<float>(w, off + q * pitch);
+  }
+}
+
 // Row indices of a lane: rv = element row is real (< M); rc = row clamped
 // below M, for row-major [M][.] buffers; rr = row for the row-minor [.][mp]
 // buffers.  Dense lanes keep groups of 4 consecutive rows whole so 16-byte
@@ -196,7 +341,7 @@ __device__ inline void lane_rows(const int (&rows)[R], int M, int mp, int (&rr)[
 template <int R, bool PE>
 __device__ inline void gather_cuts(const CutCol& cc, const float* __restrict__ gammaT, int mp, const int (&jq)[R],
                                    const bool (&jv)[R], const int (&rr)[R], float (&sG)[R], float (&sH)[R],
-                                   float (&sQ)[R], const int2* rg_pre = nullptr) {
+                                   float (&sQ)[R], const int2* rg_pre) {
 #pragma unroll
   for (int q = 0; q < R; ++q) sG[q] = sH[q] = sQ[q] = 0.f;
   if (!cc.rng) return;
@@ -388,6 +533,45 @@ struct BoundEpi {
       konst = h;
     }
   }
+  // load and apply for one sub-tile of a layer launch, from what fetch_pre and
+  // tile_cuts gave; want: the row constant is asked for
+  static constexpr int kPre = PI ? 0 : 1;            // reads alpha
+  __device__ __forceinline__ void tile(const float (&val)[4], const SubPre& p, const TileLane& t, const float (&sG)[4],
+                                       const float (&sH)[4], const float (&sQ)[4], double (&rs)[4], bool want) const {
+    const NodeDev& nd = a.nd;
+    const int rk = kind_rank(p.kind);
+    float tadd[4] = {0.f, 0.f, 0.f, 0.f}, aoff[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.acc_in) tile_acc<T>(a.acc_in, a.acc_t, nd, t, aoff);
+    if (p.mask[0] | p.mask[1] | p.mask[2] | p.mask[3]) {   // split neurons: rare
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = p.mask[q];
+        if (m && t.rl + q < t.rows) {
+          const float bv = a.rp.beta[(size_t)(t.m0 + t.rl + q) * a.rp.K + (m > 0 ? m - 1 : -m - 1)];
+          tadd[q] = m > 0 ? -bv : bv;
+        }
+      }
+    }
+    float lam[4], ah[4], konst[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ah[q] = val[q] + (aoff[q] + sG[q]);
+      relax(tile_cls(p, q), ah[q], sH[q] + tadd[q], sQ[q], p.al[q], p.rec.x, p.rec.y, p.rec.z, 0.f, lam[q], konst[q]);
+    }
+    const uint32_t pL = nd.ld * (uint32_t)sizeof(T), oL = lane_off(t, t.jv, nd.ld, t.j, sizeof(T));
+    const uint32_t pU = nd.uld * (uint32_t)sizeof(T);
+    const uint32_t oU = lane_off(t, t.jv && rk >= 0, nd.uld, rk - nd.rank0, sizeof(T));
+    const RowWin wL = row_win(a.lam_out, t.m0, t.rows, pL), wU = row_win(a.ahat_out, t.m0, t.rows, pU);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      win_st<T>(wL, oL + q * pL, to_t<T>(lam[q]));
+      win_st<T>(wU, oU + q * pU, to_t<T>(ah[q]));
+    }
+    if (want && t.jv) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) rs[q] += (double)lam[q] * (double)p.rec.w + (double)konst[q];
+    }
+  }
   template <int R, int TN, bool PE>
   __device__ inline void apply(const Frag<R, TN, PE>& f, const LaneCoords<R, TN, PE>& lc,
                                const float (&val)[TN][R], double (&rs)[R], int M, int N) const {
@@ -426,6 +610,7 @@ struct BoundEpi {
 template <typename T>
 struct AhatEpi {
   BoundEpiArgs a;
+  static constexpr int kPre = 0;
   static constexpr bool kColPre = true;
   __device__ inline const NodeDev& col_node() const { return a.nd; }
   __device__ inline const CutCol& col_cuts() const { return a.cc; }
@@ -479,6 +664,7 @@ struct AhatEpi {
 // constant, sign(v) for the adjoint, input-cut gradient pieces.
 struct ConcEpi {
   ConcEpiArgs a;
+  static constexpr int kPre = 0;
   static constexpr bool kColPre = false;
   template <int R, int TN, bool PE> struct Frag {
     int rr[R], rc[R];
@@ -505,7 +691,7 @@ struct ConcEpi {
 #pragma unroll
       for (int q = 0; q < (PE ? R : 1); ++q) f.xj[k][q] = a.x0[jq[q]];
       float sH[R], sQ[R];
-      gather_cuts<R, PE>(a.cc, a.rp.gammaT, a.rp.mp, jq, jv, f.rr, f.sG[k], sH, sQ);
+      gather_cuts<R, PE>(a.cc, a.rp.gammaT, a.rp.mp, jq, jv, f.rr, f.sG[k], sH, sQ, nullptr);
     }
   }
   template <int R, int TN, bool PE>
@@ -668,6 +854,71 @@ struct AdjEpi {
       gA = dL * p;
     }
   }
+  // load and apply for one sub-tile of a layer launch, from operands fetched ahead
+  static constexpr int kPre = PI ? 0 : 3;            // reads alpha, a_hat and, when Adam runs, alpha's moments
+  __device__ __forceinline__ void tile(const float (&val)[4], const SubPre& p, const TileLane& t, const float (&)[4],
+                                       const float (&)[4], const float (&sQ)[4], double (&)[4], bool) const {
+    const NodeDev& nd = a.nd;
+    const RowParams& rp = a.rp;
+    const int rk = kind_rank(p.kind);
+    float pre[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.acc_in) tile_acc<T>(a.acc_in, a.acc_t, nd, t, pre);
+    float dA[4], dL[4], dS[4], gA[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float gR;
+      dL[q] = a.gemm_scale * val[q] + p.addv + pre[q];
+      derive(tile_cls(p, q), dL[q], p.ah[q], sQ[q], p.al[q], p.rec.x, p.rec.y, p.rec.z, 0.f, dA[q], dS[q], gA[q], gR);
+    }
+    // cut-gradient pieces: the four rows lie below mp together; rows in
+    // [M, mp) are padding of the contribution buffer, never read.  (Before
+    // the stores: this loop's loads would wait for them.)
+    if (a.contrib && a.cc.rng && t.any()) {
+      for (int e = p.rng.x; e < p.rng.y; ++e) {
+        const float4 en = a.cc.ent[e];
+        float4 v;
+        v.x = en.y * dA[0] + en.x * dL[0] + en.z * dS[0];
+        v.y = en.y * dA[1] + en.x * dL[1] + en.z * dS[1];
+        v.z = en.y * dA[2] + en.x * dL[2] + en.z * dS[2];
+        v.w = en.y * dA[3] + en.x * dL[3] + en.z * dS[3];
+        *(float4*)(a.contrib + (size_t)a.cc.pos[e] * rp.mp + (t.m0 + t.rl)) = v;
+      }
+    }
+    if (p.mask[0] | p.mask[1] | p.mask[2] | p.mask[3]) {   // split neurons: rare
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = p.mask[q];
+        if (m && t.rl + q < t.rows)
+          beta_grad((size_t)(t.m0 + t.rl + q) * rp.K + (m > 0 ? m - 1 : -m - 1), m > 0 ? -dL[q] : dL[q]);
+      }
+    }
+    const uint32_t pL = nd.ld * (uint32_t)sizeof(T), oL = lane_off(t, t.jv, nd.ld, t.j, sizeof(T));
+    const RowWin wL = row_win(a.dahat_out, t.m0, t.rows, pL);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) win_st<T>(wL, oL + q * pL, to_t<T>(dA[q]));
+    const uint32_t pA = rp.n_I * 4u, oA = lane_off(t, t.jv && rk >= 0, rp.n_I, rk, 4);
+    if (a.adam.enabled) {
+      const GCP_CONSTANT_AS float* ac = cst(a.adam.consts);
+      const float lr_a = ac[0], ibc1 = ac[2], ibc2 = ac[3];
+      const float b1 = a.adam.b1, b2 = a.adam.b2, aeps = a.adam.eps;
+      const RowWin wm = row_win(a.m_alpha, t.m0, t.rows, pA), wv = row_win(a.v_alpha, t.m0, t.rows, pA);
+      const RowWin wa = row_win(a.alpha_rw, t.m0, t.rows, pA);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float mm = b1 * p.ma[q] + (1.f - b1) * gA[q];
+        const float vv = b2 * p.va[q] + (1.f - b2) * gA[q] * gA[q];
+        const float stp = adam_step(lr_a, mm, vv, ibc1, ibc2, aeps);
+        const float al = fminf(fmaxf(p.al[q] + stp, 0.f), 1.f);
+        win_st(wm, oA + q * pA, mm);
+        win_st(wv, oA + q * pA, vv);
+        win_st(wa, oA + q * pA, al);
+      }
+    } else {
+      const RowWin wg = row_win(a.d_alpha, t.m0, t.rows, pA);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) win_st(wg, oA + q * pA, gA[q]);
+    }
+  }
   // d/d beta of one split slot: the Adam step in place, or the gradient out
   __device__ inline void beta_grad(size_t ib, float gB) const {
     if (a.adam.enabled) {
@@ -783,6 +1034,7 @@ struct AdjEpi {
 // out = scale * GEMM (+ acc_in): partial sums of a node with several edges
 struct StoreEpi {
   StoreEpiArgs a;
+  static constexpr int kPre = 0;
   static constexpr bool kColPre = false;
   template <int R, int TN, bool PE> struct Frag {
     int rc[R];

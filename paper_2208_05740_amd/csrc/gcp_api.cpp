@@ -131,7 +131,7 @@ std::string cls_name(const char* kind, int bf16, int sign, int cfg) {
   int bm = 0, bn = 0;
   if (cfg >= 0) gemm_config_tile(cfg, &bm, &bn);
   std::string n = std::string(kind) + (bf16 ? ".bf16" : ".fp32") + (sign ? ".sign" : "");
-  if (cfg >= 0) n += ".t" + std::to_string(bm) + "x" + std::to_string(bn);
+  if (cfg >= 0) n += ".t" + std::to_string(bm) + "x" + std::to_string(bn) + (gemm_config_direct(cfg) ? "d" : "");
   return n;
 }
 
@@ -653,7 +653,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
 // trial (same inputs, outputs that the real launch overwrites, or scratch)
 // timed with HIP events, and the fastest is cached per (kind, precision,
 // sign input, M, N, K).  GCP_AUTOTUNE=0 selects a fixed heuristic instead.
-const int kTileCandidates[] = {0, 1, 2, 4, 5, 6, 7};   // 128x128 spills with the fused epilogues
+const int kTileCandidates[] = {0, 1, 2, 4, 5, 6, 7};
 
 bool autotune_enabled() {
   const char* e = std::getenv("GCP_AUTOTUNE");
@@ -661,7 +661,7 @@ bool autotune_enabled() {
 }
 
 int heuristic_cfg(int M, int N) {
-  static const int order[] = {1, 2, 0, 4, 5, 6, 7};
+  static const int order[] = {0, 4, 5, 6, 7};
   for (int c : order) {
     int bm, bn;
     gemm_config_tile(c, &bm, &bn);

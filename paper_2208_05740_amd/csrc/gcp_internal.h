@@ -124,6 +124,7 @@ hipError_t launch_gemm(int bf16, int cfg, EpiKind kind, const GemmArgs& g, const
                        hipStream_t st);
 int gemm_num_configs();
 void gemm_config_tile(int cfg, int* bm, int* bn);
+bool gemm_config_direct(int cfg);   // K loop without LDS staging (profiler class names)
 // Several GEMM problems of one instantiation (cfg, kind, sign, precision) in
 // one launch: device tables d_gs[np], d_epis[np] (the kind's *EpiArgs) and
 // d_prefix[np + 1] of cumulative tile counts (total_tiles = d_prefix[np]).

@@ -22,12 +22,22 @@ __global__ void __launch_bounds__(WM * WN * 64) gemm_epi_kernel(GemmArgs g, Epi 
   gemm_tile<T, BM, BN, WM, WN, BK, SIGN, Epi>(g, epi, xcd_tile(blockIdx.x, total));
 }
 
+// (six waves per SIMD for the one-sub-tile waves: their registers allow it)
+template <typename T, int TM, int TN, int WM, int WN, int D, bool SIGN, class Epi>
+__global__ void __launch_bounds__(WM * WN * 64, TM * TN == 1 ? 6 : 1) layer_kernel(GemmArgs g, Epi epi) {
+  __shared__ LayerLds<T, TM, TN, WM, WN, D> sm;
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
+  const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
+  layer_tile<T, TM, TN, WM, WN, D, SIGN, Epi>(g, epi, xcd_tile(blockIdx.x, total), sm);
+}
+
 // Several independent GEMM problems of one kernel instantiation in one
 // launch: tiles of problem p occupy [prefix[p], prefix[p+1]) of the linear
 // tile space; each workgroup finds its problem by binary search.
-template <typename T, int BM, int BN, int WM, int WN, int BK, bool SIGN, class Epi>
-__global__ void __launch_bounds__(WM * WN * 64)
-gemm_epi_grouped(const GemmArgs* __restrict__ gs, const Epi* __restrict__ es, const int* __restrict__ prefix, int np) {
+template <typename T, int TM, int TN, int WM, int WN, int D, bool SIGN, class Epi>
+__global__ void __launch_bounds__(WM * WN * 64, TM * TN == 1 ? 6 : 1)
+layer_grouped(const GemmArgs* __restrict__ gs, const Epi* __restrict__ es, const int* __restrict__ prefix, int np) {
+  __shared__ LayerLds<T, TM, TN, WM, WN, D> sm;
   const int t = xcd_tile(blockIdx.x, prefix[np]);
   int lo = 0, hi = np - 1;
   while (lo < hi) {
@@ -36,15 +46,17 @@ gemm_epi_grouped(const GemmArgs* __restrict__ gs, const Epi* __restrict__ es, co
   }
   const GemmArgs g = gs[lo];
   const Epi e = es[lo];
-  gemm_tile<T, BM, BN, WM, WN, BK, SIGN, Epi>(g, e, t - prefix[lo]);
+  layer_tile<T, TM, TN, WM, WN, D, SIGN, Epi>(g, e, t - prefix[lo], sm);
 }
 
-// Tile configurations available to the autotuner: (BM, BN, WM, WN).
+// Tile configurations available to the autotuner: (BM, BN), direct or staged
+// K loop.
 struct TileCfg { int bm, bn; };
-static const TileCfg kCfgs[] = {{64, 64}, {128, 64}, {64, 128}, {128, 128}, {32, 64}, {32, 32}, {16, 64}, {16, 32}};
+static const TileCfg kCfgs[] = {{64, 64}, {32, 32}, {16, 64}, {64, 64}, {32, 64}, {32, 32}, {16, 64}, {16, 32}};
 static_assert(sizeof(kCfgs) / sizeof(kCfgs[0]) == 8, "tile table");
 int gemm_num_configs() { return (int)(sizeof(kCfgs) / sizeof(kCfgs[0])); }
 void gemm_config_tile(int cfg, int* bm, int* bn) { *bm = kCfgs[cfg].bm; *bn = kCfgs[cfg].bn; }
+bool gemm_config_direct(int cfg) { return cfg == 1 || cfg == 2 || cfg == 7; }
 
 // Launch target: a single problem (GemmArgs by value) or a group (device
 // tables of arguments and tile prefix sums).
@@ -57,18 +69,22 @@ struct GemmLaunch {
   int np, total_tiles;
 };
 
-template <typename T, int BM, int BN, int WM, int WN, bool SIGN, class Epi, class Args>
-static hipError_t launch_cfg(const GemmLaunch& L, hipStream_t st) {
-  constexpr int BK = (sizeof(T) == 4) ? 64 : 128;
+// K steps whose fragments a direct tile's wave holds ahead: three in the
+// adjoint, whose epilogue operands take the registers of the fourth
+template <class Epi> constexpr int kDepth = Epi::kPre == 3 ? 3 : 4;
+
+template <typename T, int TM, int TN, int WM, int WN, int D, bool SIGN, class Epi, class Args>
+static hipError_t launch_layer(const GemmLaunch& L, hipStream_t st) {
   if (L.d_gs) {
     if (L.total_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL((gemm_epi_grouped<T, BM, BN, WM, WN, BK, SIGN, Epi>), dim3((unsigned)L.total_tiles),
+    hipLaunchKernelGGL((layer_grouped<T, TM, TN, WM, WN, D, SIGN, Epi>), dim3((unsigned)L.total_tiles),
                        dim3(WM * WN * 64), 0, st, L.d_gs, (const Epi*)L.d_es, L.d_prefix, L.np);
     return hipGetLastError();
   }
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16;
   const GemmArgs& g = *L.g;
   const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
-  hipLaunchKernelGGL((gemm_epi_kernel<T, BM, BN, WM, WN, BK, SIGN, Epi>), dim3((unsigned)tiles),
+  hipLaunchKernelGGL((layer_kernel<T, TM, TN, WM, WN, D, SIGN, Epi>), dim3((unsigned)tiles),
                      dim3(WM * WN * 64), 0, st, g, Epi{*(const Args*)L.epi});
   return hipGetLastError();
 }
@@ -76,14 +92,13 @@ static hipError_t launch_cfg(const GemmLaunch& L, hipStream_t st) {
 template <typename T, bool SIGN, class Epi, class Args>
 static hipError_t launch_any(int cfg, const GemmLaunch& L, hipStream_t st) {
   switch (cfg) {
-    case 0: return launch_cfg<T, 64, 64, 2, 2, SIGN, Epi, Args>(L, st);
-    case 1: return launch_cfg<T, 128, 64, 2, 2, SIGN, Epi, Args>(L, st);
-    case 2: return launch_cfg<T, 64, 128, 2, 2, SIGN, Epi, Args>(L, st);
-    case 3: return launch_cfg<T, 128, 128, 2, 2, SIGN, Epi, Args>(L, st);
-    case 4: return launch_cfg<T, 32, 64, 2, 2, SIGN, Epi, Args>(L, st);
-    case 5: return launch_cfg<T, 32, 32, 2, 2, SIGN, Epi, Args>(L, st);
-    case 6: return launch_cfg<T, 16, 64, 1, 4, SIGN, Epi, Args>(L, st);
-    case 7: return launch_cfg<T, 16, 32, 1, 2, SIGN, Epi, Args>(L, st);
+    case 0: case 3: return launch_layer<T, 2, 2, 2, 2, 0, SIGN, Epi, Args>(L, st);
+    case 1: return launch_layer<T, 1, 1, 2, 2, kDepth<Epi>, SIGN, Epi, Args>(L, st);
+    case 2: return launch_layer<T, 1, 1, 1, 4, kDepth<Epi>, SIGN, Epi, Args>(L, st);
+    case 4: return launch_layer<T, 1, 2, 2, 2, 0, SIGN, Epi, Args>(L, st);
+    case 5: return launch_layer<T, 1, 1, 2, 2, 0, SIGN, Epi, Args>(L, st);
+    case 6: return launch_layer<T, 1, 1, 1, 4, 0, SIGN, Epi, Args>(L, st);
+    case 7: return launch_layer<T, 1, 1, 1, 2, kDepth<Epi>, SIGN, Epi, Args>(L, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -107,6 +122,16 @@ static hipError_t launch_typed(int cfg, EpiKind kind, int sign, const GemmLaunch
 // Explicit-pi epilogues (rho set): instantiated for the small tiles only
 // (their fragments carry rho and its moments); a large-tile choice runs as
 // 32x32.
+template <typename T, int BM, int BN, int WM, int WN, bool SIGN, class Epi, class Args>
+static hipError_t launch_cfg(const GemmLaunch& L, hipStream_t st) {
+  constexpr int BK = (sizeof(T) == 4) ? 64 : 128;
+  const GemmArgs& g = *L.g;
+  const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
+  hipLaunchKernelGGL((gemm_epi_kernel<T, BM, BN, WM, WN, BK, SIGN, Epi>), dim3((unsigned)tiles),
+                     dim3(WM * WN * 64), 0, st, g, Epi{*(const Args*)L.epi});
+  return hipGetLastError();
+}
+
 template <typename T, bool SIGN, class Epi, class Args>
 static hipError_t launch_small(int cfg, const GemmLaunch& L, hipStream_t st) {
   switch (cfg) {
