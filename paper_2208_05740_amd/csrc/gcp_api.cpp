@@ -730,13 +730,14 @@ bool conv_direct_enabled() {
   const char* e = std::getenv("GCP_CONV_DIRECT");
   return !(e && e[0] == '0');
 }
+// The direct kernel wherever it exists, without a trial: it adds in another
+// order than the slab kernels, so a choice by timing would let a bound's last
+// bits depend on the batch size.  (It is the faster one in fp32 and in bf16
+// from about 2000 rows; below, the slab kernels take up to a few microseconds
+// less.)
 Cands conc_conv_cands(const ConvGeom& g, const ConvPlan& plan) {
-  Cands c = conv_cands();
-  if (conv_direct_enabled() && conv_direct_ok(g, plan, EPI_CONC)) {
-    c.list.push_back(kConvDirectCfg);
-    c.fallback = kConvDirectCfg;
-  }
-  return c;
+  if (conv_direct_enabled() && conv_direct_ok(g, plan, EPI_CONC)) return Cands{{kConvDirectCfg}, kConvDirectCfg};
+  return conv_cands();
 }
 // Explicit-pi launches: the shapes their epilogues are instantiated for, and
 // tile-cache keys of their own (epilogue kind + kPiKey).
