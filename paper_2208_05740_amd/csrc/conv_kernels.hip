@@ -461,13 +461,13 @@ struct BandOps<BoundEpi<T, PI>> {
     e.template apply_to<kRows, 1, false>(fr, lc, val, rs, M, size, BandSink<T>{cell, r0});
   }
   template <int V>
-  __device__ static inline void stream(const BoundEpi<T, PI>& e, int j, const float (&v)[V][kRows], int r0, int M,
+  __device__ static inline void stream(const BoundEpi<T, PI>& e, int j, const float (&v)[V][kRows], int r0, int M, bool want,
                                        double (&rs)[kRows]) {
     const NodeDev& nd = e.a.nd;
     int kv[V];
     float bj[V], pre[kRows][V];
     get_kind<V>(nd, e.a.cc, j, kv);
-    get_f32<V>(nd.bias + j, bj);
+    if (want) get_f32<V>(nd.bias + j, bj);
     if (e.a.acc_in) {
 #pragma unroll
       for (int q = 0; q < kRows; ++q)
@@ -481,7 +481,7 @@ struct BandOps<BoundEpi<T, PI>> {
       for (int k = 0; k < V; ++k) {
         const float ah = v[k][q] + (e.a.acc_in ? pre[q][k] : 0.f);
         o[k] = kv[k] & kListed ? v[k][q] : (kind_cls(kv[k]) == ACTIVE ? ah : 0.f);
-        if (!(kv[k] & kListed)) rs[q] += (double)o[k] * (double)bj[k];
+        if (want && !(kv[k] & kListed)) rs[q] += (double)o[k] * (double)bj[k];
       }
       put<T, V>((T*)e.a.lam_out + (size_t)(r0 + q) * nd.ld + j, o);
     }
@@ -511,7 +511,7 @@ struct BandOps<AdjEpi<T, PI>> {
     e.template apply_to<kRows, 1, false>(fr, lc, val, rs, M, size, BandSink<T>{cell, r0});
   }
   template <int V>
-  __device__ static inline void stream(const AdjEpi<T, PI>& e, int j, const float (&v)[V][kRows], int r0, int M,
+  __device__ static inline void stream(const AdjEpi<T, PI>& e, int j, const float (&v)[V][kRows], int r0, int M, bool want,
                                        double (&rs)[kRows]) {
     if (!e.a.dahat_out) return;
     const NodeDev& nd = e.a.nd;
@@ -541,7 +541,7 @@ struct BandOps<AdjEpi<T, PI>> {
 template <> struct BandOps<StoreEpi> {
   static constexpr bool kLists = false, kStream = true;
   template <int V>
-  __device__ static inline void stream(const StoreEpi& e, int j, const float (&v)[V][kRows], int r0, int M,
+  __device__ static inline void stream(const StoreEpi& e, int j, const float (&v)[V][kRows], int r0, int M, bool want,
                                        double (&rs)[kRows]) {
     float pre[kRows][V];
     if (e.a.acc_in) {
@@ -588,11 +588,11 @@ template <> struct BandOps<ConcEpi> {
     }
   }
   template <int V>
-  __device__ static inline void stream(const ConcEpi& e, int j, const float (&v)[V][kRows], int r0, int M,
+  __device__ static inline void stream(const ConcEpi& e, int j, const float (&v)[V][kRows], int r0, int M, bool want,
                                        double (&rs)[kRows]) {
     double xj[V];
 #pragma unroll
-    for (int k = 0; k < V; ++k) xj[k] = e.a.x0[j + k];
+    for (int k = 0; k < V; ++k) xj[k] = want ? e.a.x0[j + k] : 0.0;
 #pragma unroll
     for (int q = 0; q < kRows; ++q) {
       if (r0 + q >= M) break;
@@ -600,7 +600,7 @@ template <> struct BandOps<ConcEpi> {
 #pragma unroll
       for (int k = 0; k < V; ++k) {
         const double vd = (double)v[k][q];
-        rs[q] += xj[k] * vd - e.a.eps * fabs(vd);
+        if (want) rs[q] += xj[k] * vd - e.a.eps * fabs(vd);
         sg[k] = (v[k][q] > 0.f) ? 1 : ((v[k][q] < 0.f) ? -1 : 0);
       }
       if (!e.a.sign_out) continue;
@@ -667,7 +667,7 @@ __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan&
         float v[V][kRows];
 #pragma unroll
         for (int k = 0; k < V; ++k) *(float4*)v[k] = outs[n * P.OS + off + k];
-        BandOps<Epi>::template stream<V>(epi, n * HWe + j0 + off, v, r0, c.M, rs);
+        BandOps<Epi>::template stream<V>(epi, n * HWe + j0 + off, v, r0, c.M, c.partial != nullptr, rs);
       }
     };
     if (per_ch % 4 == 0 && HWe % 4 == 0 && j0 % 4 == 0) walk(std::integral_constant<int, 4>{});
@@ -676,8 +676,7 @@ __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan&
   if (c.partial) {
 #pragma unroll
     for (int q = 0; q < kRows; ++q) {
-      double tsum = rs[q];
-      for (int o = 32; o > 0; o >>= 1) tsum += __shfl_xor(tsum, o, 64);
+      const double tsum = wave_sum64(rs[q]);
       if (lane == 0) red[wave * kRows + q] = tsum;
     }
     __syncthreads();

@@ -431,7 +431,12 @@ __device__ __forceinline__ void sub_epilogue(const GemmArgs& g, const Epi& epi, 
     } else {
       epi.template load<4, 1, false>(fr, lc, g.M, g.N);
     }
-    epi.template apply<4, 1, false>(fr, lc, val, rs, g.M, g.N);
+    if (g.partial) {
+      epi.template apply<4, 1, false>(fr, lc, val, rs, g.M, g.N);
+    } else {                 // the row constants are not asked for: dead is never read
+      double dead[4] = {0.0, 0.0, 0.0, 0.0};
+      epi.template apply<4, 1, false>(fr, lc, val, dead, g.M, g.N);
+    }
   }
 }
 
@@ -623,15 +628,18 @@ __device__ __forceinline__ void bound_elem_rows(const float* bcast, const void* 
   for (int q = 0; q < R; ++q) rs[q] = 0.0;
   typename BoundEpi<T, PI>::template Frag<R, 1, false> fr;
   epi.template load<R, 1, false>(fr, lc, M, a.nd.size);
+  if (!partial) {            // the row constants are not asked for: rs is dead here
+    epi.template apply<R, 1, false>(fr, lc, val, rs, M, a.nd.size);
+    return;
+  }
   epi.template apply<R, 1, false>(fr, lc, val, rs, M, a.nd.size);
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    double t = rs[q];
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    const double t = wave_sum64(rs[q]);
     if ((tx & 63) == 0) red[q][tx >> 6] = t;
   }
   __syncthreads();
-  if (tx < R && partial) {
+  if (tx < R) {
     const int q = tx, r = r0 + q;
     if (r < M) partial[(size_t)(slot0 + cb) * a.rp.mp + r] = (red[q][0] + red[q][1]) + (red[q][2] + red[q][3]);
   }
