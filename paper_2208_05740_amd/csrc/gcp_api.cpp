@@ -1455,6 +1455,44 @@ void set_plan(const Call& c, int eid, ConvArgs& ca) {
 const void* wt_bound(const EdgeH& E, int bf16) { return bf16 ? E.WT16.p : E.WT32.p; }
 const void* w_adj(const EdgeH& E, int bf16) { return bf16 ? E.W16.p : E.W32.p; }
 
+// ---------------------------------------------------------------- start of a call
+// The small independent jobs of a call's start, gathered into one launch.
+struct Prologue {
+  hipStream_t st;
+  PrepJob jobs[kPrepMax];
+  int n = 0;
+  explicit Prologue(hipStream_t s) : st(s) {}
+  void add(const PrepJob& j) {
+    if (n == kPrepMax) flush();
+    jobs[n++] = j;
+  }
+  void flush() {
+    hip_check(launch_prep(jobs, n, st), "kernel launch (start of a call)");
+    n = 0;
+  }
+  void transpose(const float* in, int rows, int cols, float* out, int ld_out) {
+    add(PrepJob{PREP_TRANSPOSE, 0, in, nullptr, nullptr, out, rows, cols, cols, ld_out, ConvGeom{}});
+  }
+  void zero(float* p, int rows, int cols) { add(PrepJob{PREP_ZERO, 0, nullptr, nullptr, nullptr, p, rows, cols, 0, 0, ConvGeom{}}); }
+  // C b_out of every spec row
+  void out_const(const Call& c) {
+    const NodeH& on = c.net->nodes[c.net->out];
+    add(PrepJob{PREP_CONST, 0, c.C, on.bias.p, nullptr, c.ws->cb.p, c.S, on.size, 0, 0, ConvGeom{}});
+  }
+  // the output in its c-hat form: C b_out and C W per in-edge
+  void constants(Call& c) {
+    gcp_net* net = c.net;
+    const NodeH& on = net->nodes[net->out];
+    out_const(c);
+    for (int eid : on.in_edges) {
+      const EdgeH& E = *net->edges[eid];
+      add(PrepJob{PREP_CHAT, E.kind == GCP_EDGE_IDENTITY ? 2 : 0, c.C, E.Wraw.p, nullptr,
+                  c.ws->chat.as<float>() + c.ws->chat_off[E.src], c.S, on.size, E.d_src, net->nodes[E.src].ld, ConvGeom{}});
+    }
+    c.consts_done = true;
+  }
+};
+
 // ---------------------------------------------------------------- bound pass
 // Processes nodes from the output backwards.  For each target p the pushes
 // from its consumers are accumulated into acc[p] except the last one, which
@@ -1512,7 +1550,9 @@ struct BoundPass {
       // Lambda^(out) = C on every row, pushed through the output's edges
       if (c.rec) fail(GCP_EUNSUPPORTED, "grouped launches need the c-hat form of the output");
       if (!dry && !c.consts_done) {
-        check(launch_out_const(c.C, c.S, on.size, on.bias.as<float>(), ws.cb.as<double>(), c.st));
+        Prologue pr(c.st);
+        pr.out_const(c);
+        pr.flush();
         check(launch_spec_rows(bf16, c.C, c.S, on.size, c.M, ws.lam[net->out]->p, on.ld, c.st));
       }
       for (int eid : on.in_edges)
@@ -1521,13 +1561,9 @@ struct BoundPass {
         if (net->edges[eid]->kind != GCP_EDGE_IDENTITY) push(eid);
     }
     if (!net->out_general && !dry && !c.rec && !c.consts_done) {
-      check(launch_out_const(c.C, c.S, on.size, on.bias.as<float>(), ws.cb.as<double>(), c.st));
-      for (int eid : on.in_edges) {
-        const EdgeH& E = *net->edges[eid];
-        float* ch = ws.chat.as<float>() + ws.chat_off[E.src];
-        check(launch_chat(c.C, c.S, on.size, E.Wraw.as<float>(), E.d_src,
-                          E.kind == GCP_EDGE_IDENTITY ? 2 : 0, ch, net->nodes[E.src].ld, c.st));
-      }
+      Prologue pr(c.st);
+      pr.constants(c);
+      pr.flush();
     }
     for (int eid : net->out_general ? std::vector<int>{} : on.in_edges) {
       const EdgeH& E = *net->edges[eid];
@@ -1773,7 +1809,7 @@ struct AdjPass {
 
   // add vectors of the nodes fed by the input: bias + A x0, once per call
   // (the other nodes add their bias, read in place: add_vec_of)
-  void prepare() {
+  void prepare(Prologue& pr) {
     gcp_net* net = c.net;
     auto& ws = *c.ws;
     for (int i = 0; i < net->out; ++i) {
@@ -1783,8 +1819,9 @@ struct AdjPass {
         const EdgeH& E = *net->edges[eid];
         if (E.src >= 0) continue;
         int kind = E.kind == GCP_EDGE_DENSE ? 0 : (E.kind == GCP_EDGE_CONV ? 1 : 2);
-        check(launch_wx0(&E.cg, kind, E.Wraw.as<float>(), n.size, net->in_size, c.x0,
-                         seeded ? nullptr : n.bias.as<float>(), ws.addv[i]->as<float>(), c.st));
+        if (seeded) pr.flush();     // adds to what the first edge's job writes
+        pr.add(PrepJob{PREP_WX0, kind, E.Wraw.p, c.x0, seeded ? nullptr : n.bias.p, ws.addv[i]->p, n.size, net->in_size, 0, 0,
+                       E.cg});
         seeded = true;
       }
     }
@@ -2277,14 +2314,23 @@ void bound_impl(const gcp_net* net_c, const double* x0, double eps, const double
     carve_static(c, sws, bf16, grads);
   }
   if (mode & GCP_FLAG_VALIDATE) validate_params(c, alpha, beta, gamma);
-  if (c.N > 0) hip_check(launch_transpose(gamma, c.M, c.N, c.N, c.ws->gammaT.as<float>(), c.rp.mp, c.st), "transpose");
+  AdjPass ap{c, bf16, AdamArgs{0, 0.f, 0.f, 0.f, nullptr}, d_alpha, d_beta, nullptr, nullptr,
+             nullptr, nullptr, nullptr, nullptr, rho ? d_rho : nullptr};
+  const size_t n_beta = (size_t)c.M * splits->K;
+  const bool beta_late = d_beta && beta && d_beta < beta + n_beta && beta < d_beta + n_beta;
+  Prologue pr(c.st);
+  if (c.N > 0) pr.transpose(gamma, c.M, c.N, c.ws->gammaT.as<float>(), c.rp.mp);
+  if (!net->out_general) pr.constants(c);
+  if (grads) {
+    // (an output in beta's own memory is cleared after the bound pass has read it)
+    if (!beta_late) pr.zero(d_beta, c.M, splits->K);
+    ap.prepare(pr);
+  }
+  pr.flush();
   if (grads && !no_alloc) plan_ahat(c, mode);
   bound_pass(c, bf16, grads, grads && c.nnz > 0, bound, verified);
   if (grads) {
-    if (splits->K > 0) hip_check(launch_fill_f32(d_beta, (int64_t)c.M * splits->K, 0.f, c.st), "fill");
-    AdjPass ap{c, bf16, AdamArgs{0, 0.f, 0.f, 0.f, nullptr}, d_alpha, d_beta, nullptr, nullptr,
-               nullptr, nullptr, nullptr, nullptr, rho ? d_rho : nullptr};
-    ap.prepare();
+    if (beta_late) hip_check(launch_fill_f32(d_beta, (int64_t)n_beta, 0.f, c.st), "fill");
     ap.run();
     if (c.rp.N > 0)
       hip_check(timed(c.st, "gamma_grad", Bytes{(double)c.M * (c.nnz * 4.0 + c.rp.N * 4.0), (double)c.M * c.rp.N * 8.0},
@@ -2347,15 +2393,6 @@ void run_chain(Call& c, int bf16, const ChainPlan& pl, float* alpha, float* beta
   gcp_net* net = c.net;
   auto& ws = *c.ws;
   const int L = net->out;
-  if (!c.consts_done) {
-    const NodeH& on = net->nodes[net->out];
-    hip_check(launch_out_const(c.C, c.S, on.size, on.bias.as<float>(), ws.cb.as<double>(), c.st), "out const");
-    const EdgeH& E = *net->edges[on.in_edges[0]];
-    hip_check(launch_chat(c.C, c.S, on.size, E.Wraw.as<float>(), E.d_src, 0, ws.chat.as<float>() + ws.chat_off[E.src],
-                          net->nodes[E.src].ld, c.st),
-              "c-hat");
-    c.consts_done = true;
-  }
   ws.chain_host.resize(L);
   double flops = 0.0, elems = 0.0;
   for (int i = 0; i < L; ++i) {
@@ -2412,22 +2449,6 @@ void run_chain(Call& c, int bf16, const ChainPlan& pl, float* alpha, float* beta
                   [&] { return launch_chain_opt(bf16, a, tiles, pl.lds, c.st); }),
             "fused chain");
 }
-
-// constants of the output layer for one call (c-hat = C W, C b_out)
-void launch_constants(Call& c) {
-  gcp_net* net = c.net;
-  auto& ws = *c.ws;
-  if (net->out_general) fail(GCP_EUNSUPPORTED, "grouped launches need the c-hat form of the output");
-  const NodeH& on = net->nodes[net->out];
-  hip_check(launch_out_const(c.C, c.S, on.size, on.bias.as<float>(), ws.cb.as<double>(), c.st), "out const");
-  for (int eid : on.in_edges) {
-    const EdgeH& E = *net->edges[eid];
-    hip_check(launch_chat(c.C, c.S, on.size, E.Wraw.as<float>(), E.d_src, E.kind == GCP_EDGE_IDENTITY ? 2 : 0,
-                          ws.chat.as<float>() + ws.chat_off[E.src], net->nodes[E.src].ld, c.st),
-              "c-hat");
-  }
-}
-
 // Whether a call's iterations can run as one persistent launch: every edge
 // dense (the recorded schedule is GEMM, elementwise and multiplier steps over
 // rows), the output in the c-hat form, Lemma A.1's pi*, a_hat stored.
@@ -2475,11 +2496,14 @@ void optimize_impl(const gcp_net* net_c, const double* x0, double eps, const dou
   hip_check(launch_adam_table(ws.adam_tab.as<float>(), opt->iters, opt->lr_alpha, opt->lr_mult, opt->decay,
                               opt->adam_b1, opt->adam_b2, c.st),
             "adam table");
-  if (N > 0) hip_check(launch_transpose(gamma, c.M, (int)N, (int)N, ws.gammaT.as<float>(), c.rp.mp, c.st), "transpose");
   size_partials(c, bf16, true, c.nnz > 0);
   {
+    Prologue pr(c.st);
+    if (N > 0) pr.transpose(gamma, c.M, (int)N, ws.gammaT.as<float>(), c.rp.mp);
+    if (!net->out_general) pr.constants(c);
     AdjPass prep{c, bf16, adam, nullptr, nullptr, alpha, beta, ma, va, mb, vb, nullptr, rho, mr, vr};
-    prep.prepare();
+    prep.prepare(pr);
+    pr.flush();
   }
   auto iteration = [&](Call& cc, int t) {   // t < 0: the step counter gives t (graph replay)
     AdamArgs ad = adam;
@@ -2531,14 +2555,12 @@ void optimize_impl(const gcp_net* net_c, const double* x0, double eps, const dou
     std::vector<uintptr_t> key = plan_key();
     key.push_back((uintptr_t)persist_xcd_sync(persist_queues()));
     if (ws.pplan && ws.pplan->key == key) {
-      launch_constants(c);
       run_persist(*ws.pplan, bf16, opt->iters, 0, tab, c.st);
       done = opt->iters;
       persist_latch = ws.pplan->latch.as<int>();
     } else {
       iteration(c, 0);   // tunes the per-layer tiles the schedule records, sizes buffers
       done = 1;
-      c.consts_done = true;
       key = plan_key();
       key.push_back((uintptr_t)persist_xcd_sync(persist_queues()));
       Recorder rec;
@@ -3052,12 +3074,14 @@ extern "C" int gcp_optimize_batch(int32_t n_all, const gcp_batch_item* items_all
     Moments& m = mom[i];
     m.ma = it.adam_state; m.va = m.ma + M * nI; m.mb = m.va + M * nI; m.vb = m.mb + M * K;
     m.mg = m.vb + M * K; m.vg = m.mg + M * N;
-    if (N > 0) hip_check(launch_transpose(it.gamma, c.M, (int)N, (int)N, c.net->ws.gammaT.as<float>(), c.rp.mp, st),
-                         "transpose");
     size_partials(c, bf16, true, c.nnz > 0);
-    launch_constants(c);
+    if (c.net->out_general) fail(GCP_EUNSUPPORTED, "grouped launches need the c-hat form of the output");
+    Prologue pr(st);
+    if (N > 0) pr.transpose(it.gamma, c.M, (int)N, c.net->ws.gammaT.as<float>(), c.rp.mp);
+    pr.constants(c);
     AdjPass prep{c, bf16, adam, nullptr, nullptr, it.alpha, it.beta, m.ma, m.va, m.mb, m.vb};
-    prep.prepare();
+    prep.prepare(pr);
+    pr.flush();
     for (uintptr_t v : {(uintptr_t)it.net, (uintptr_t)it.x0, (uintptr_t)it.C, (uintptr_t)it.S,
                         (uintptr_t)it.splits->id, (uintptr_t)(c.cuts ? c.cuts->id : 0), (uintptr_t)it.alpha,
                         (uintptr_t)it.beta,
@@ -3306,19 +3330,15 @@ extern "C" int gcp_crown_bounds_domain(const gcp_net_desc* desc, const double* x
     if (K) Zd.alloc((size_t)rows * K * 4);
     Ad.alloc(std::max<size_t>((size_t)rows * nI * 4, 4));
     Bd.alloc((size_t)rows * 8);
-    std::vector<float> arows((size_t)rows * nI);
-    for (int r = 0; r < rows; ++r) std::copy(arow.begin(), arow.end(), arows.begin() + (size_t)r * nI);
-    if (nI) hip_check(hipMemcpyAsync(Ad.p, arows.data(), arows.size() * 4, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
-    std::vector<double> Ch((size_t)rows * d), bh(rows);
+    if (nI) {
+      hip_check(hipMemcpyAsync(Ad.p, arow.data(), nI * 4, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+      hip_check(launch_repeat_row(Ad.as<float>(), rows, (int)nI, st), "slope rows");
+    }
+    std::vector<double> bh(rows);
     std::vector<double> lo(d), hi(d);
     for (int s0 = 0; s0 < S_all; s0 += rows) {
       const int S = std::min(rows, S_all - s0);
-      std::fill(Ch.begin(), Ch.end(), 0.0);
-      for (int r = 0; r < S; ++r) {
-        const int g = s0 + r;
-        Ch[(size_t)r * d + (g < d ? g : g - d)] = g < d ? 1.0 : -1.0;
-      }
-      hip_check(hipMemcpyAsync(Cd.p, Ch.data(), (size_t)S * d * 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+      hip_check(launch_unit_rows(Cd.as<double>(), S, d, s0, st), "unit spec rows");
       const int rc = gcp_bound(net.p, x0, eps, Cd.as<double>(), S, spl.p, nullptr, nI ? Ad.as<float>() : nullptr,
                                K ? Zd.as<float>() : nullptr, nullptr, mode & (0xff | GCP_FLAG_OUTWARD),
                                Bd.as<double>(), nullptr, nullptr,

@@ -217,14 +217,29 @@ int conv_num_configs();
 constexpr int kConvDirectCfg = 6;
 bool conv_direct_ok(const ConvGeom& g, const ConvPlan& plan, EpiKind kind);
 
-hipError_t launch_chat(const double* C, int S, int d_out, const float* W, int d_in,
-                       int kind, float* chat, int ld, hipStream_t st);
-hipError_t launch_out_const(const double* C, int S, int d_out, const float* bias,
-                            double* cb, hipStream_t st);
+// Small independent jobs of a call's start, in one launch.
+enum PrepKind { PREP_CONST, PREP_CHAT, PREP_WX0, PREP_TRANSPOSE, PREP_ZERO };
+struct PrepJob {
+  int kind, mode;          // mode: edge kind (0 dense, 1 conv, 2 identity)
+  const void *a, *b, *c;   // CONST: C, bias; CHAT: C, W; WX0: W, x0, bias or null (add to out); TRANSPOSE: in
+  void* out;
+  int n0, n1, n2, n3;      // CONST: S, d_out; CHAT: S, d_out, d_in, pitch; WX0: d_out, d_in;
+                           // TRANSPOSE: rows, cols, pitch in, pitch out; ZERO: n0 x n1 floats
+  ConvGeom cg;             // WX0 of a conv
+};
+constexpr int kPrepMax = 16;
+struct PrepArgs {
+  int n;
+  int first[kPrepMax];     // first workgroup of each job
+  PrepJob job[kPrepMax];
+};
+hipError_t launch_prep(const PrepJob* jobs, int n, hipStream_t st);
+// rows g0 .. g0 + rows - 1 of {e_0 .. e_(d-1), -e_0 .. -e_(d-1)}, [rows][d]
+hipError_t launch_unit_rows(double* C, int rows, int d, int g0, hipStream_t st);
+// row 0 of p [rows][n] repeated in the others
+hipError_t launch_repeat_row(float* p, int rows, int n, hipStream_t st);
 // out[r][j] = C[r mod S][j] in the operand type, r < M, j < d
 hipError_t launch_spec_rows(int bf16, const double* C, int S, int d, int M, void* out, int ld, hipStream_t st);
-hipError_t launch_wx0(const ConvGeom* cg, int kind, const float* W, int d_out, int d_in,
-                      const double* x0, const float* bias, float* out, hipStream_t st);
 hipError_t launch_reduce_rows(int M, int mp, int S, const double* partial, int n_slots,
                               const double* cb, const float* gammaT, int N, const double* d,
                               double* bound, uint8_t* verified, hipStream_t st);

@@ -274,37 +274,6 @@ hipError_t launch_identity_acc(int bf16_mode, int M, int size, const void* src, 
 }
 
 // ------------------------------------------------------------------ small kernels
-// chat[s][j] = sum_o C[s][o] * W[o][j]  (dense output edge), or C[s][j]
-// (identity), accumulated in fp64.
-__global__ void chat_kernel(const double* C, int S, int d_out, const float* W, int d_in, int kind,
-                            float* chat, int ld) {
-  int s = blockIdx.y;
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d_in) return;
-  double acc = 0.0;
-  if (kind == 2) {
-    acc = C[(size_t)s * d_out + j];
-  } else {
-    for (int o = 0; o < d_out; ++o) acc += C[(size_t)s * d_out + o] * (double)W[(size_t)o * d_in + j];
-  }
-  chat[(size_t)s * ld + j] = (float)acc;
-}
-
-hipError_t launch_chat(const double* C, int S, int d_out, const float* W, int d_in, int kind, float* chat,
-                       int ld, hipStream_t st) {
-  dim3 grid((d_in + 255) / 256, S);
-  hipLaunchKernelGGL(chat_kernel, grid, dim3(256), 0, st, C, S, d_out, W, d_in, kind, chat, ld);
-  return hipGetLastError();
-}
-
-__global__ void out_const_kernel(const double* C, int S, int d_out, const float* bias, double* cb) {
-  int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= S) return;
-  double acc = 0.0;
-  for (int o = 0; o < d_out; ++o) acc += C[(size_t)s * d_out + o] * (double)bias[o];
-  cb[s] = acc;
-}
-
 // Lambda of the output node materialised: row r = C[r mod S] in the operand
 // type (for outputs whose in-edges the c-hat shortcut cannot take).
 template <typename T>
@@ -329,21 +298,70 @@ hipError_t launch_spec_rows(int bf16_mode, const double* C, int S, int d, int M,
   return hipGetLastError();
 }
 
-hipError_t launch_out_const(const double* C, int S, int d_out, const float* bias, double* cb, hipStream_t st) {
-  hipLaunchKernelGGL(out_const_kernel, dim3((S + 63) / 64), dim3(64), 0, st, C, S, d_out, bias, cb);
-  return hipGetLastError();
+// What a call needs before its first pass, and what depends on nothing the
+// passes compute: a few small independent jobs.  A launch each cost 3 to 8 us
+// with its gap, of which the jobs themselves take a fraction, so one launch
+// runs them side by side, each on its own range of workgroups: gradient calls
+// 54 -> 46.6 us (8-neuron MLP, one domain), 108 -> 86.5 (784-256x6 MLP, 333
+// rows, bf16, with the row sums' loads in flight together), 241 -> 201 (CNN).
+//
+// transpose: [rows][cols] (pitch ld_in) -> [cols][ld_out], 32x32 tiles through LDS
+__device__ inline void transpose_tile(const float* in, int rows, int cols, int ld_in, float* out, int ld_out, int bx,
+                                      int by, float (&t)[32][33]) {
+  const int c0 = bx * 32, r0 = by * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int y = ty; y < 32; y += 8) {
+    const int r = r0 + y, c = c0 + tx;
+    t[y][tx] = (r < rows && c < cols) ? in[(size_t)r * ld_in + c] : 0.f;
+  }
+  __syncthreads();
+  for (int y = ty; y < 32; y += 8) {
+    const int c = c0 + y, r = r0 + tx;
+    if (c < cols && r < rows) out[(size_t)c * ld_out + r] = t[tx][y];
+  }
 }
-
+// n values of step `by`, kBatch loads in flight at a time, added in order
+template <int kBatch, class F>
+__device__ inline double sum_strided(int first, int n, int by, F term) {
+  double acc = 0.0;
+  int k = first;
+  for (; k + (kBatch - 1) * by < n; k += kBatch * by) {
+    double v[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) v[i] = term(k + i * by);
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) acc += v[i];
+  }
+  for (; k < n; k += by) acc += term(k);
+  return acc;
+}
+// cb[s] = C[s] . bias, one wave per spec row (a thread per row summed 4096
+// terms of an intermediate bound's rows in 392 us)
+__device__ inline void out_const_rows(const double* C, int S, int d, const float* bias, double* cb, int b) {
+  const int s = b * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (s >= S) return;
+  const double acc = wave_sum64(sum_strided<4>(lane, d, 64, [&](int o) { return C[(size_t)s * d + o] * (double)bias[o]; }));
+  if (lane == 0) cb[s] = acc;
+}
+// chat[s][j] = sum_o C[s][o] * W[o][j]  (dense output edge), or C[s][j]
+// (identity, kind 2), accumulated in fp64
+__device__ inline void chat_cols(const double* C, int d_out, const float* W, int d_in, int kind, float* chat, int ld, int s,
+                                 int bx) {
+  const int j = bx * 256 + threadIdx.x;
+  if (j >= d_in) return;
+  const double* c = C + (size_t)s * d_out;
+  chat[(size_t)s * ld + j] =
+      (float)(kind == 2 ? c[j] : sum_strided<8>(0, d_out, 1, [&](int o) { return c[o] * (double)W[(size_t)o * d_in + j]; }));
+}
 // out[j] = (bias ? bias[j] : out[j]) + (A x0)_j for an edge from the network
-// input, fp64 sums; one wave per output, lanes stride over the inputs.
-__global__ void __launch_bounds__(256) wx0_kernel(ConvGeom cg, int kind, const float* W, int d_out, int d_in,
-                                                  const double* x0, const float* bias, float* out) {
-  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+// input, fp64 sums; one wave per output, lanes stride over the inputs
+__device__ inline void wx0_rows(const ConvGeom& cg, int kind, const float* W, int d_out, int d_in, const double* x0,
+                                const float* bias, float* out, int b) {
+  const int j = b * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (j >= d_out) return;
   double acc = 0.0;
   if (kind == 0) {
-    for (int k = lane; k < d_in; k += 64) acc += (double)W[(size_t)j * d_in + k] * x0[k];
+    acc = sum_strided<4>(lane, d_in, 64, [&](int k) { return (double)W[(size_t)j * d_in + k] * x0[k]; });
   } else if (kind == 1) {
     const int o = j / (cg.ho * cg.wo), y = (j / cg.wo) % cg.ho, x = j % cg.wo;
     const int taps = cg.ci * cg.kh * cg.kw;
@@ -356,22 +374,99 @@ __global__ void __launch_bounds__(256) wx0_kernel(ConvGeom cg, int kind, const f
   } else if (lane == 0) {
     acc = x0[j];
   }
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  acc = wave_sum64(acc);
   if (lane == 0) out[j] = (float)((bias ? (double)bias[j] : (double)out[j]) + acc);
 }
 
-hipError_t launch_wx0(const ConvGeom* cg, int kind, const float* W, int d_out, int d_in, const double* x0,
-                      const float* bias, float* out, hipStream_t st) {
-  ConvGeom g = cg ? *cg : ConvGeom{};
-  hipLaunchKernelGGL(wx0_kernel, dim3((d_out + 3) / 4), dim3(256), 0, st, g, kind, W, d_out, d_in, x0, bias, out);
+__global__ void __launch_bounds__(256) prep_kernel(PrepArgs a) {
+  __shared__ float t[32][33];
+  int i = 0;
+  while (i + 1 < a.n && (int)blockIdx.x >= a.first[i + 1]) ++i;
+  const PrepJob& p = a.job[i];
+  const int b = blockIdx.x - a.first[i];
+  switch (p.kind) {
+    case PREP_CONST: out_const_rows((const double*)p.a, p.n0, p.n1, (const float*)p.b, (double*)p.out, b); break;
+    case PREP_CHAT: {
+      const int nx = (p.n2 + 255) / 256;
+      chat_cols((const double*)p.a, p.n1, (const float*)p.b, p.n2, p.mode, (float*)p.out, p.n3, b / nx, b % nx);
+      break;
+    }
+    case PREP_WX0:
+      wx0_rows(p.cg, p.mode, (const float*)p.a, p.n0, p.n1, (const double*)p.b, (const float*)p.c, (float*)p.out, b);
+      break;
+    case PREP_TRANSPOSE: {
+      const int nx = (p.n1 + 31) / 32;
+      transpose_tile((const float*)p.a, p.n0, p.n1, p.n2, (float*)p.out, p.n3, b % nx, b / nx, t);
+      break;
+    }
+    case PREP_ZERO: {
+      const size_t n = (size_t)p.n0 * p.n1, e = (size_t)b * 1024 + threadIdx.x;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (e + 256 * q < n) ((float*)p.out)[e + 256 * q] = 0.f;
+      break;
+    }
+  }
+}
+
+static long prep_blocks(const PrepJob& p) {
+  switch (p.kind) {
+    case PREP_CONST: case PREP_WX0: return (p.n0 + 3) / 4;
+    case PREP_CHAT: return (long)p.n0 * ((p.n2 + 255) / 256);
+    case PREP_TRANSPOSE: return (long)((p.n0 + 31) / 32) * ((p.n1 + 31) / 32);
+    case PREP_ZERO: return ((long)p.n0 * p.n1 + 1023) / 1024;
+  }
+  return 0;
+}
+
+hipError_t launch_prep(const PrepJob* jobs, int n, hipStream_t st) {
+  if (n > kPrepMax) return hipErrorInvalidValue;
+  PrepArgs a{};
+  long at = 0;
+  for (int i = 0; i < n; ++i) {
+    const long nb = prep_blocks(jobs[i]);
+    if (nb <= 0) continue;
+    a.first[a.n] = (int)at;
+    a.job[a.n++] = jobs[i];
+    at += nb;
+    if (at > 0x7fffffffL) return hipErrorInvalidValue;
+  }
+  if (at == 0) return hipSuccess;
+  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)at), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+// Spec rows of intermediate bounds, made on the device: row r is e_g for
+// g = g0 + r < d, else -e_(g - d).  A workgroup per row; 4096 rows of 4096 in
+// 16 us.  Filled on the host and uploaded from pageable memory, the rows of
+// the CNN's two conv layers (335 MB) were most of its intermediate bounds'
+// 63.9 ms, now 10.5.
+__global__ void __launch_bounds__(256) unit_rows_kernel(double* C, int d, int g0) {
+  const int g = g0 + blockIdx.x, j1 = g < d ? g : g - d;
+  const double v = g < d ? 1.0 : -1.0;
+  for (int j = threadIdx.x; j < d; j += 256) C[(size_t)blockIdx.x * d + j] = j == j1 ? v : 0.0;
+}
+hipError_t launch_unit_rows(double* C, int rows, int d, int g0, hipStream_t st) {
+  if (rows <= 0 || d <= 0) return hipSuccess;
+  hipLaunchKernelGGL(unit_rows_kernel, dim3(rows), dim3(256), 0, st, C, d, g0);
+  return hipGetLastError();
+}
+
+// row 0 of an [rows][n] array into rows 1 .. rows - 1, a workgroup per row
+__global__ void __launch_bounds__(256) repeat_row_kernel(float* p, int n) {
+  for (int j = threadIdx.x; j < n; j += 256) p[(size_t)(blockIdx.x + 1) * n + j] = p[j];
+}
+hipError_t launch_repeat_row(float* p, int rows, int n, hipStream_t st) {
+  if (rows <= 1 || n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(repeat_row_kernel, dim3(rows - 1), dim3(256), 0, st, p, n);
   return hipGetLastError();
 }
 
 // bound[r] = sum_slots partial[slot][r] + c_s.b_out - gamma_r.d.  A block
 // takes kRedRows rows; each row's slots and cuts are split over kRedParts
-// threads (every kRedParts-th one, coalesced over rows) whose sums are
-// combined in a fixed order, so the result is deterministic.
-constexpr int kRedRows = 32, kRedParts = 8;
+// threads (every kRedParts-th one, coalesced over rows, eight loads in flight)
+// whose sums are combined in a fixed order, so the result is deterministic.
+constexpr int kRedRows = 16, kRedParts = 16;
 __global__ void __launch_bounds__(256) reduce_rows_kernel(int M, int mp, int S, const double* partial, int n_slots,
                                                           const double* cb, const float* gammaT, int N,
                                                           const double* d, double* bound, uint8_t* verified) {
@@ -380,8 +475,8 @@ __global__ void __launch_bounds__(256) reduce_rows_kernel(int M, int mp, int S, 
   const int r = blockIdx.x * kRedRows + rl;
   double s = 0.0;
   if (r < M) {
-    for (int k = part; k < n_slots; k += kRedParts) s += partial[(size_t)k * mp + r];
-    for (int k = part; k < N; k += kRedParts) s -= (double)gammaT[(size_t)k * mp + r] * d[k];
+    s = sum_strided<8>(part, n_slots, kRedParts, [&](int k) { return partial[(size_t)k * mp + r]; });
+    s -= sum_strided<8>(part, N, kRedParts, [&](int k) { return (double)gammaT[(size_t)k * mp + r] * d[k]; });
   }
   sh[part][rl] = s;
   __syncthreads();
@@ -542,21 +637,10 @@ hipError_t launch_gamma_update(int M, int mp, int N, const int32_t* row_ptr, con
   return hipGetLastError();
 }
 
-// [rows][cols] (pitch ld_in) -> [cols][ld_out], 32x32 tiles through LDS
 __global__ void __launch_bounds__(256) transpose_kernel(const float* in, int rows, int cols, int ld_in, float* out,
                                                         int ld_out) {
   __shared__ float t[32][33];
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int y = ty; y < 32; y += 8) {
-    const int r = r0 + y, c = c0 + tx;
-    t[y][tx] = (r < rows && c < cols) ? in[(size_t)r * ld_in + c] : 0.f;
-  }
-  __syncthreads();
-  for (int y = ty; y < 32; y += 8) {
-    const int c = c0 + y, r = r0 + tx;
-    if (c < cols && r < rows) out[(size_t)c * ld_out + r] = t[tx][y];
-  }
+  transpose_tile(in, rows, cols, ld_in, out, ld_out, blockIdx.x, blockIdx.y, t);
 }
 
 hipError_t launch_transpose(const float* in, int rows, int cols, int ld_in, float* out, int ld_out, hipStream_t st) {
