@@ -531,50 +531,101 @@ __global__ void __launch_bounds__(256) slack_weights_kernel(SlackArgs a) {
   a.wcomb[n.off + k] = w;
 }
 
+// Rows of a wave in slack_rows_kernel: four share each weight (8 bytes a
+// neuron from the L2, twice an fp32 Lambda) and each 16 bytes of gammaT.
+// The certifying pass of the 784-256x6 MLP, 36864 rows: 685 -> 632 us, of
+// which this kernel took 108 (226 MB of Lambda: 50 at the rate of a large copy).
+constexpr int kSlackRows = 4;
+
+// acc[q] += sum |lam[q ld + k]| w[k], four neurons per lane and step
 template <typename T>
-__device__ inline double abs_dot(const T* lam, const double* w, int size, int lane) {
-  double s = 0.0;
-  for (int k = lane; k < size; k += 64) s += fabs((double)from_t<T>(lam[k])) * w[k];
-  return s;
+__device__ inline void abs_dot(const T* const (&lam)[kSlackRows], const double* w, int size, int lane,
+                               double (&acc)[kSlackRows]) {
+  typedef typename std::conditional<sizeof(T) == 4, uint4, uint2>::type V;
+  for (int k = lane * 4; k < size; k += 256) {
+    T e[kSlackRows][4];
+    double wk[4];
+    if (k + 4 <= size) {
+#pragma unroll
+      for (int q = 0; q < kSlackRows; ++q) *(V*)e[q] = *(const V*)(lam[q] + k);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wk[i] = w[k + i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool in = k + i < size;
+        wk[i] = in ? w[k + i] : 0.0;
+#pragma unroll
+        for (int q = 0; q < kSlackRows; ++q) e[q][i] = in ? lam[q][k + i] : to_t<T>(0.f);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kSlackRows; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[q] += fabs((double)from_t<T>(e[q][i])) * wk[i];
+  }
 }
 
-// One wave per row: the row's slack (sum |Lambda| w over its nodes, the
-// spec-row term, |beta| and |gamma| terms), written negated into its
+// One wave per kSlackRows rows: a row's slack (sum |Lambda| w over its nodes,
+// the spec-row term, |beta| and |gamma| terms), written negated into its
 // partial slot.  Lanes stride over the neurons; the wave's sum is combined
 // in a fixed order.
 __global__ void __launch_bounds__(256) slack_rows_kernel(SlackArgs a) {
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= a.M) return;
+  const int r0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kSlackRows;
+  if (r0 >= a.M) return;
   const double xin = a.wcomb[a.total];
-  const int s = r % a.S, b = r / a.S;
-  double acc = 0.0;
-  for (int i = 0; i < a.n_nodes; ++i) {
-    const SlackNode& n = a.nodes[i];
-    if (!n.lam) continue;
-    const double* w = a.wcomb + n.off;
-    if (a.bf16) acc += abs_dot((const bf16*)n.lam + (size_t)r * n.ld, w, n.size, lane);
-    else acc += abs_dot((const float*)n.lam + (size_t)r * n.ld, w, n.size, lane);
+  int r[kSlackRows];           // rows past the end repeat the last one
+  double acc[kSlackRows];
+  bool bad[kSlackRows];
+#pragma unroll
+  for (int q = 0; q < kSlackRows; ++q) {
+    r[q] = min(r0 + q, a.M - 1);
+    acc[q] = 0.0;
+    bad[q] = false;
   }
-  const double* Cs = a.C + (size_t)s * a.d_out;
-  bool bad = false;
-  for (int k = lane; k < a.d_out; k += 64) {
-    const double c = Cs[k];
-    if (a.out_chat) acc += fabs(c) * a.wcomb[a.out_off + k];
-    else {   // the materialised output Lambda must be C itself
-      const double held = a.bf16 ? (double)(float)to_t<bf16>((float)c) : (double)(float)c;
-      bad |= held != c;
+  auto nodes = [&](auto t) {
+    typedef decltype(t) T;
+    for (int i = 0; i < a.n_nodes; ++i) {
+      const SlackNode& n = a.nodes[i];
+      if (!n.lam) continue;
+      const T* lam[kSlackRows];
+#pragma unroll
+      for (int q = 0; q < kSlackRows; ++q) lam[q] = (const T*)n.lam + (size_t)r[q] * n.ld;
+      abs_dot<T>(lam, a.wcomb + n.off, n.size, lane, acc);
     }
+  };
+  if (a.bf16) nodes(bf16{});
+  else nodes(float{});
+#pragma unroll
+  for (int q = 0; q < kSlackRows; ++q) {
+    const double* Cs = a.C + (size_t)(r[q] % a.S) * a.d_out;
+    for (int k = lane; k < a.d_out; k += 64) {
+      const double c = Cs[k];
+      if (a.out_chat) acc[q] += fabs(c) * a.wcomb[a.out_off + k];
+      else {   // the materialised output Lambda must be C itself
+        const double held = a.bf16 ? (double)(float)to_t<bf16>((float)c) : (double)(float)c;
+        bad[q] |= held != c;
+      }
+    }
+    const int b = r[q] / a.S;
+    for (int k = lane; k < a.K; k += 64)
+      acc[q] += a.c_beta * fabs((double)a.beta[(size_t)r[q] * a.K + k]) * a.zsplit[(size_t)b * a.K + k];
   }
-  for (int k = lane; k < a.K; k += 64)
-    acc += a.c_beta * fabs((double)a.beta[(size_t)r * a.K + k]) * a.zsplit[(size_t)b * a.K + k];
   for (int c = lane; c < a.N; c += 64) {
-    const double g = fabs((double)a.gammaT[(size_t)c * a.mp + r]);
-    acc += g * (a.c_cut * (a.kap[c] + xin * a.kap[a.N + c]) + a.c_d * a.kap[2 * a.N + c]);
+    const float4 g = *(const float4*)(a.gammaT + (size_t)c * a.mp + r0);   // (r0 + 3 < mp, a multiple of 16)
+    const double kc = a.c_cut * (a.kap[c] + xin * a.kap[a.N + c]) + a.c_d * a.kap[2 * a.N + c];
+    acc[0] += fabs((double)g.x) * kc;
+    acc[1] += fabs((double)g.y) * kc;
+    acc[2] += fabs((double)g.z) * kc;
+    acc[3] += fabs((double)g.w) * kc;
   }
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  bad = __any(bad);
-  if (lane == 0) a.out[r] = bad ? -INFINITY : -(acc * (1.0 + 0x1p-40));
+#pragma unroll
+  for (int q = 0; q < kSlackRows; ++q) {
+    const double t = wave_sum64(acc[q]);
+    const bool any = __any(bad[q]);
+    if (lane == 0 && r0 + q < a.M) a.out[r0 + q] = any ? -INFINITY : -(t * (1.0 + 0x1p-40));
+  }
 }
 
 hipError_t launch_slack(const SlackArgs& a, hipStream_t st) {
