@@ -130,6 +130,52 @@ static void plan_bands(ConvPlan& P, int trans, int bh) {
   }
 }
 
+// What a slab launch's workgroup looks up, laid out once per net and band as
+// it lies in LDS: the slab offset of each K index relative to a GEMM row's
+// base [KP], base (low half) and result offset (high half, 0xffff: none) of
+// each GEMM row [16 MT], phase of each 16-row tile [MT] and the number of
+// tiles.  Made by every workgroup, with their integer divisions, these were
+// part of what a workgroup costs apart from its data; with the lists' first
+// entries fetched ahead of the slab (band_epilogue) the ascent of the 3x32x32
+// ResNet, 4608 rows in bf16, went from 72.1 to 66.9 ms.
+__host__ __device__ static inline int table_words(const ConvPlan& P) { return P.KP + 16 * P.MT + (P.MT + 1 + 3) / 4 * 4; }
+std::vector<int32_t> conv_tables(const ConvPlan& P, int trans) {
+  const int words = table_words(P);
+  std::vector<int32_t> all((size_t)words * P.n_bands, 0);
+  const int s = P.s, p = P.p;
+  const int safe_base = trans ? (P.A - 1) * P.Wp + P.Bn - 1 : 0;    // in-slab for every K offset
+  for (int band = 0; band < P.n_bands; ++band) {
+    int32_t *koff = all.data() + (size_t)band * words, *desc = koff + P.KP, *tph = desc + 16 * P.MT;
+    for (int k = 0; k < P.Kreal; ++k) {
+      const int ch = k / (P.A * P.Bn), a = (k / P.Bn) % P.A, b = k % P.Bn;
+      koff[k] = trans ? ch * P.CHS - a * P.Wp - b : ch * P.CHS + a * P.Wp + b;
+    }
+    std::fill(desc, desc + 16 * P.MT, (int32_t)((uint32_t)safe_base | 0xffff0000u));
+    const int yb0 = band * P.BH, yb1 = std::min(P.He, yb0 + P.BH);
+    const int sy0 = trans ? (yb0 + p) / s - (P.A - 1) : yb0 * s - p;   // source row of slab row 0
+    int ntile = 0;
+    // GEMM rows of the band, phase by phase, each phase padded to whole tiles
+    for (int ph = 0; ph < P.n_phase; ++ph) {
+      int yf, ny, xf, nx;
+      phase_rows(P, ph, yb0, yb1, trans != 0, &yf, &ny, &xf, &nx);
+      const int npos = ny * nx, nt = (npos + 15) / 16, ry = ph / s, rx = ph % s;
+      const int base0 = trans ? ((yf + p - ry) / s - sy0) * P.Wp + (xf + p - rx) / s + P.xl
+                              : (yf * s - p - sy0) * P.Wp + xf * s - p + P.xl;
+      const int rstep = trans ? P.Wp : s * P.Wp, cstep = trans ? 1 : s, st = trans ? s : 1;
+      const int out0 = (yf - yb0) * P.We + xf;
+      for (int i = 0; i < npos; ++i) {
+        const int iy = i / nx, ix = i - iy * nx;
+        desc[ntile * 16 + i] = (int32_t)((uint32_t)(base0 + iy * rstep + ix * cstep) |
+                                         ((uint32_t)(out0 + iy * st * P.We + ix * st) << 16));
+      }
+      for (int i = 0; i < nt; ++i) tph[ntile + i] = ph;
+      ntile += nt;
+    }
+    tph[P.MT] = ntile;
+  }
+  return all;
+}
+
 // The direct transposed conv: shapes it is built for, the 64-position chunks
 // of a band (at most), and the channels it stages at a time.
 static bool direct_shape(const ConvPlan& P) {
@@ -249,7 +295,7 @@ static bool conv_alias(const ConvPlan& P, int nw, int tn) {
 
 static int conv_lds_bytes(const ConvPlan& P, int esz, int nw, bool alias) {
   const int slab = align16(P.rb * (int)slab_cells(P) * esz), outs = align16((int)out_cells(P) * 16);
-  return align16(P.KP * 4) + align16(nw * 8 * kRows) + align16(P.MT * 4) + align16(P.MT * 16 * 4) +
+  return align16(nw * 8 * kRows) + table_words(P) * 4 +
          (alias ? std::max(slab, outs) : slab + outs);
 }
 
@@ -614,14 +660,54 @@ template <> struct BandOps<ConcEpi> {
 template <class Epi>
 __device__ inline const CutCol& band_cuts(const Epi& e) { return e.a.cc; }
 
+// The band's lists as one: the unstable neurons, then the stable ones with
+// cut entries; entry i < n is {neuron, kind}.
+struct BandList {
+  const int2 *uns, *cut;
+  int n_u, n;
+  __device__ inline BandList(const ConvArgs& c, int band) {
+    const int u0 = c.uns ? c.uns_off[band] : 0, c0 = c.cut ? c.cut_off[band] : 0;
+    uns = c.uns + u0;
+    cut = c.cut + c0;
+    n_u = c.uns ? c.uns_off[band + 1] - u0 : 0;
+    n = n_u + (c.cut ? c.cut_off[band + 1] - c0 : 0);
+  }
+  __device__ inline int2 at(int i) const { return i < n_u ? uns[i] : cut[i - n_u]; }
+};
+
+// A thread's current list entry and what the epilogue reads for it.
+struct BandItem {
+  int2 e;
+  SubPre p;
+};
+template <typename T, class Epi>
+__device__ __forceinline__ TileLane band_lane(const ConvArgs& c, int r0, int j, bool has) {
+  return TileLane{r0, min(kRows, c.M - r0), 0, j, j, has};
+}
+// entry i (past the end: the last one, whose values are not used)
+template <typename T, class Epi>
+__device__ __forceinline__ void fetch_item(const ConvArgs& c, const Epi& epi, const BandList& l, int r0, int i, BandItem& it) {
+  if constexpr (BandOps<Epi>::kLists) {
+    if (l.n == 0) return;
+    it.e = l.at(min(i, l.n - 1));
+    it.p.kind = it.e.y;
+    it.p.rng = make_int2(0, 0);
+    const int2* rng = band_cuts(epi).rng;
+    if (rng) it.p.rng = rng[it.e.x];
+    if constexpr (Epi::kPre > 0) fetch_pre<T>(epi, band_lane<T, Epi>(c, r0, it.e.x, i < l.n), it.p);
+  }
+}
+
 // Fused epilogue of one workgroup's band over the results of its kRows batch
 // rows in LDS (cell n * OS + position of channel n; position (y - yb0) * We +
 // x), then the row constant of each batch row into its partial slot slot0 +
-// band.  e0: this thread's first entry of the unstable list (fetched before
-// the GEMM, so that its latency is hidden).
-template <int NW, class Epi>
+// band.  it: this thread's first list entry, fetched before the GEMM so that
+// its loads (three round trips: entry, kind and cut range, alpha and moments)
+// arrive under the slab's.
+template <typename T, int NW, class Epi>
 __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan& P, const Epi& epi, float4* outs,
-                                              double* red, int r0, int band, int yb0, int yb1, int2 e0) {
+                                              double* red, int r0, int band, int yb0, int yb1, const BandList& list,
+                                              BandItem& it) {
   constexpr int NT = NW * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int HWe = P.He * P.We;
@@ -632,26 +718,30 @@ __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan&
   for (int q = 0; q < kRows; ++q) rs[q] = 0.0;
   if constexpr (BandOps<Epi>::kLists) {
     const float inv_hw = 1.f / (float)HWe;
-    LaneCoords<kRows, 1, false> lc;
+    for (int i = tid; i < list.n; i += NT) {
+      if (i != tid) fetch_item<T>(c, epi, list, r0, i, it);
+      int off;
+      const int n = div_rem(it.e.x, HWe, inv_hw, &off);
+      float4& cell = outs[n * P.OS + off - j0];
+      const float4 v = cell;
+      if constexpr (Epi::kPre > 0) {
+        const TileLane t = band_lane<T, Epi>(c, r0, it.e.x, true);
+        float sG[4], sH[4], sQ[4];
+        tile_cuts(epi.a.cc, epi.a.rp, t, it.p, sG, sH, sQ);
+        const float val[4] = {v.x, v.y, v.z, v.w};
+        epi.tile(val, it.p, t, sG, sH, sQ, rs, c.partial != nullptr, [&](int q, T o) { ((float*)&cell)[q] = from_t<T>(o); });
+      } else {
+        LaneCoords<kRows, 1, false> lc;
 #pragma unroll
-    for (int q = 0; q < kRows; ++q) lc.r[q] = r0 + q;
-    auto walk = [&](const int2* list, int b, int end, bool first) {
-      for (int i = b + tid; i < end; i += NT) {
-        const int2 e = first && i == b + tid ? e0 : list[i];
-        int off;
-        const int n = div_rem(e.x, HWe, inv_hw, &off);
-        float4& cell = outs[n * P.OS + off - j0];
+        for (int q = 0; q < kRows; ++q) lc.r[q] = r0 + q;
+        lc.j[0][0] = it.e.x;
         ColPre<1> pre;
-        pre.kind[0] = e.y;
-        pre.rng[0] = band_cuts(epi).rng ? band_cuts(epi).rng[e.x] : make_int2(0, 0);
-        lc.j[0][0] = e.x;
-        const float4 v = cell;
+        pre.kind[0] = it.e.y;
+        pre.rng[0] = it.p.rng;
         const float val[1][kRows] = {{v.x, v.y, v.z, v.w}};
         BandOps<Epi>::run(epi, lc, pre, val, (float*)&cell, r0, c.M, size, rs);
       }
-    };
-    if (c.uns) walk(c.uns, c.uns_off[band], c.uns_off[band + 1], true);
-    if (c.cut) walk(c.cut, c.cut_off[band], c.cut_off[band + 1], false);
+    }
     if constexpr (BandOps<Epi>::kStream) __syncthreads();
   }
   if constexpr (BandOps<Epi>::kStream) {
@@ -688,16 +778,6 @@ __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan&
   }
 }
 
-// this thread's first entry of the band's unstable list
-__device__ inline int2 first_listed(const ConvArgs& c, int band) {
-  int2 e = make_int2(0, 0);
-  if (c.uns) {
-    const int i = c.uns_off[band] + (int)threadIdx.x;
-    if (i < c.uns_off[band + 1]) e = c.uns[i];
-  }
-  return e;
-}
-
 template <typename T, int NW, int TN, int RB, bool TRANS, bool SIGN, class Epi>
 __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan P, Epi epi, int alias) {
   constexpr int NT = NW * 64;
@@ -706,11 +786,14 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
   typedef typename Cell<T, RB>::type CellT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* sp = smem;
-  int* koff = (int*)sp;           sp += align16(P.KP * 4);
   double* red = (double*)sp;      sp += align16(NW * 8 * kRows);
-  int* tph = (int*)sp;            sp += align16(P.MT * 4);        // phase of each 16-row tile
-  // per GEMM row: slab base (low half), result offset (high half, 0xffff: none)
-  uint32_t* desc = (uint32_t*)sp; sp += align16(P.MT * 16 * 4);
+  // the band's tables (conv_tables): K index -> slab offset; per GEMM row: slab
+  // base (low half), result offset (high half, 0xffff: none); per 16-row tile:
+  // its phase, then the number of tiles
+  const int words = table_words(P);
+  int* koff = (int*)sp;           sp += words * 4;
+  const uint32_t* desc = (const uint32_t*)(koff + P.KP);
+  const int* tph = koff + P.KP + 16 * P.MT;
   CellT* slab = (CellT*)sp;
   float4* outs = (float4*)(alias ? sp : sp + align16(RB * P.Kch * P.CHS * (int)sizeof(T)));
 
@@ -720,48 +803,14 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
   const int s = P.s, p = P.p;
   const int yb0 = band * P.BH, yb1 = min(P.He, yb0 + P.BH);
   const int sy0 = TRANS ? (yb0 + p) / s - (P.A - 1) : yb0 * s - p;   // source row of slab row 0
-  const int safe_base = TRANS ? (P.A - 1) * P.Wp + P.Bn - 1 : 0;    // in-slab for every koff
-  const int2 e0 = first_listed(c, band);
-
-  // K index -> slab offset relative to a row's base
-  for (int k = tid; k < P.KP; k += NT) {
-    int o = 0;
-    if (k < P.Kreal) {
-      const int ch = k / (P.A * P.Bn), a = (k / P.Bn) % P.A, b = k % P.Bn;
-      o = TRANS ? ch * P.CHS - a * P.Wp - b : ch * P.CHS + a * P.Wp + b;
-    }
-    koff[k] = o;
-  }
-  // GEMM rows of the band, phase by phase, each phase padded to whole tiles
-  int ntile = 0;
-  for (int ph = 0; ph < P.n_phase; ++ph) {
-    int yf, ny, xf, nx;
-    phase_rows(P, ph, yb0, yb1, TRANS, &yf, &ny, &xf, &nx);
-    const int npos = ny * nx, nt = (npos + 15) / 16;
-    int base0, rstep, cstep;
-    if constexpr (TRANS) {
-      const int ry = ph / s, rx = ph % s;
-      base0 = ((yf + p - ry) / s - sy0) * P.Wp + (xf + p - rx) / s + P.xl;
-      rstep = P.Wp; cstep = 1;
-    } else {
-      base0 = (yf * s - p - sy0) * P.Wp + xf * s - p + P.xl;
-      rstep = s * P.Wp; cstep = s;
-    }
-    const int st = TRANS ? s : 1;
-    const int out0 = (yf - yb0) * P.We + xf;
-    for (int i = tid; i < nt * 16; i += NT) {
-      uint32_t d = (uint32_t)safe_base | 0xffff0000u;
-      if (i < npos) {
-        const int iy = i / nx, ix = i - iy * nx;
-        d = (uint32_t)(base0 + iy * rstep + ix * cstep) | ((uint32_t)(out0 + iy * st * P.We + ix * st) << 16);
-      }
-      desc[ntile * 16 + i] = d;
-    }
-    for (int i = tid; i < nt; i += NT) tph[ntile + i] = ph;
-    ntile += nt;
-  }
+  const uint4* bt = (const uint4*)(c.tab + (size_t)band * words);
+  const uint4 t0 = bt[min(tid, words / 4 - 1)];        // (in flight with the list's loads)
+  const BandList list(c, band);
+  BandItem it;
+  fetch_item<T>(c, epi, list, r0, tid, it);
+  if (tid < words / 4) ((uint4*)koff)[tid] = t0;
+  for (int i = tid + NT; i < words / 4; i += NT) ((uint4*)koff)[i] = bt[i];
   const int nck = (P.Nch + 16 * TN - 1) / (16 * TN);
-  const int items = ntile * nck;
   const int g = lane >> 4;
   const int KR = (P.Kreal + KC - 1) / KC * KC;
   for (int q0 = 0; q0 < kRows; q0 += RB) {
@@ -769,6 +818,7 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
     if (q0 > 0) __syncthreads();             // the previous rows' MFMAs are done with the slab
     stage_slab<T, SIGN, T, RB, NT>(c, P, slab, r0 + q0, sy0, 0, P.Kch);
     __syncthreads();
+    const int items = __builtin_amdgcn_readfirstlane(tph[P.MT]) * nck;
     // MFMA items: (16-row tile, column chunk of 16*TN channels), kIT per wave at a time
     for (int t0 = 0; t0 < items; t0 += NW * kIT) {
       f4 acc[kIT][RB][TN];
@@ -841,7 +891,7 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
     }
   }
   __syncthreads();
-  band_epilogue<NW>(c, P, epi, outs, red, r0, band, yb0, yb1, e0);
+  band_epilogue<T, NW>(c, P, epi, outs, red, r0, band, yb0, yb1, list, it);
 }
 
 // Transposed convolution into a source of at most four channels (the
@@ -924,7 +974,10 @@ __global__ void __launch_bounds__(kDirNW * 64) convT_direct_kernel(ConvArgs c, C
     for (int ch = 0; ch < NC; ++ch) *(f4*)(outs + ch * P.OS + coff) = acc[ch];
   }
   __syncthreads();
-  band_epilogue<kDirNW>(c, P, epi, outs, red, r0, band, yb0, yb1, make_int2(0, 0));
+  const BandList list(c, band);
+  BandItem it;
+  fetch_item<T>(c, epi, list, r0, tid, it);
+  band_epilogue<T, kDirNW>(c, P, epi, outs, red, r0, band, yb0, yb1, list, it);
 }
 
 // launch configurations: waves per workgroup x column tiles per wave
@@ -949,7 +1002,7 @@ static hipError_t conv_go(const ConvArgs& c, const ConvPlan& P, const Epi& epi, 
 template <typename T, bool TRANS, bool SIGN, class Epi>
 static hipError_t conv_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;
-  if (c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
+  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
   if (P.rb == 1) return conv_go<T, 4, 1, 1, TRANS, SIGN>(c, P, epi, st);
   if (cfg >= 0 && cfg < conv_num_configs() && !conv_alias(P, kConv[cfg].nw, kConv[cfg].tn)) cfg = 2;
   switch (cfg) {
@@ -987,7 +1040,7 @@ static hipError_t conv_typed(int cfg, EpiKind kind, const ConvArgs& c, const voi
 template <typename T, bool TRANS, bool SIGN, class Epi>
 static hipError_t conv_pi_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;
-  if (c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
+  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
   if (P.rb == 1) return conv_go<T, 4, 1, 1, TRANS, SIGN>(c, P, epi, st);
   if (cfg == 0 && conv_alias(P, 4, 1)) return conv_go<T, 4, 1, 4, TRANS, SIGN>(c, P, epi, st);
   return conv_go<T, 8, 1, 4, TRANS, SIGN>(c, P, epi, st);

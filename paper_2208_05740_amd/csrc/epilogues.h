@@ -558,11 +558,15 @@ struct BoundEpi {
       konst = h;
     }
   }
-  // load and apply for one sub-tile of a layer launch, from what fetch_pre and
-  // tile_cuts gave; want: the row constant is asked for
+  // load and apply for four rows of a lane's neuron, from what fetch_pre and
+  // tile_cuts gave; out(q, Lambda) takes the rows, want: the row constant is
+  // asked for
   static constexpr int kPre = PI ? 0 : 1;            // reads alpha
+  __device__ inline void* out_base() const { return a.lam_out; }
+  template <class Out>
   __device__ __forceinline__ void tile(const float (&val)[4], const SubPre& p, const TileLane& t, const float (&sG)[4],
-                                       const float (&sH)[4], const float (&sQ)[4], double (&rs)[4], bool want) const {
+                                       const float (&sH)[4], const float (&sQ)[4], double (&rs)[4], bool want,
+                                       const Out& out) const {
     const NodeDev& nd = a.nd;
     const int rk = kind_rank(p.kind);
     float tadd[4] = {0.f, 0.f, 0.f, 0.f}, aoff[4] = {0.f, 0.f, 0.f, 0.f};
@@ -583,13 +587,12 @@ struct BoundEpi {
       ah[q] = val[q] + (aoff[q] + sG[q]);
       relax(tile_cls(p, q), ah[q], sH[q] + tadd[q], sQ[q], p.al[q], p.rec.x, p.rec.y, p.rec.z, 0.f, lam[q], konst[q]);
     }
-    const uint32_t pL = nd.ld * (uint32_t)sizeof(T), oL = lane_off(t, t.jv, nd.ld, t.j, sizeof(T));
     const uint32_t pU = nd.uld * (uint32_t)sizeof(T);
     const uint32_t oU = lane_off(t, t.jv && rk >= 0, nd.uld, rk - nd.rank0, sizeof(T));
-    const RowWin wL = row_win(a.lam_out, t.m0, t.rows, pL), wU = row_win(a.ahat_out, t.m0, t.rows, pU);
+    const RowWin wU = row_win(a.ahat_out, t.m0, t.rows, pU);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      win_st<T>(wL, oL + q * pL, to_t<T>(lam[q]));
+      out(q, to_t<T>(lam[q]));
       win_st<T>(wU, oU + q * pU, to_t<T>(ah[q]));
     }
     if (want && t.jv) {
@@ -879,10 +882,12 @@ struct AdjEpi {
       gA = dL * p;
     }
   }
-  // load and apply for one sub-tile of a layer launch, from operands fetched ahead
+  // load and apply for four rows of a lane's neuron, as BoundEpi::tile
   static constexpr int kPre = PI ? 0 : 3;            // reads alpha, a_hat and, when Adam runs, alpha's moments
+  __device__ inline void* out_base() const { return a.dahat_out; }
+  template <class Out>
   __device__ __forceinline__ void tile(const float (&val)[4], const SubPre& p, const TileLane& t, const float (&)[4],
-                                       const float (&)[4], const float (&sQ)[4], double (&)[4], bool) const {
+                                       const float (&)[4], const float (&sQ)[4], double (&)[4], bool, const Out& out) const {
     const NodeDev& nd = a.nd;
     const RowParams& rp = a.rp;
     const int rk = kind_rank(p.kind);
@@ -917,10 +922,8 @@ struct AdjEpi {
           beta_grad((size_t)(t.m0 + t.rl + q) * rp.K + (m > 0 ? m - 1 : -m - 1), m > 0 ? -dL[q] : dL[q]);
       }
     }
-    const uint32_t pL = nd.ld * (uint32_t)sizeof(T), oL = lane_off(t, t.jv, nd.ld, t.j, sizeof(T));
-    const RowWin wL = row_win(a.dahat_out, t.m0, t.rows, pL);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) win_st<T>(wL, oL + q * pL, to_t<T>(dA[q]));
+    for (int q = 0; q < 4; ++q) out(q, to_t<T>(dA[q]));
     const uint32_t pA = rp.n_I * 4u, oA = lane_off(t, t.jv && rk >= 0, rp.n_I, rk, 4);
     if (a.adam.enabled) {
       const GCP_CONSTANT_AS float* ac = cst(a.adam.consts);

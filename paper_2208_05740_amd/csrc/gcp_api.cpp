@@ -188,9 +188,12 @@ struct DBuf {
   void ensure(size_t n) {
     if (n > bytes) alloc(n);
   }
+  // (every byte is written: no clearing, unlike alloc)
   template <class T> void upload(const std::vector<T>& v) {
-    alloc(v.size() * sizeof(T));
+    release();
     if (v.empty()) return;
+    hip_check(hipMalloc(&p, v.size() * sizeof(T)), "hipMalloc");
+    bytes = v.size() * sizeof(T);
     hip_check(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice), "hipMemcpy");
     hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
   }
@@ -225,6 +228,7 @@ struct EdgeH {
   int ldk_f = 0, ldk_t = 0;   // conv: padded K of W32/W16 (adjoint) and WT32/WT16 (bound)
   ConvPlan plan[2];           // conv: conv_plan(cg, trans)
   DBuf uns[2], uns_off[2];    // conv: unstable neurons band by band (ConvArgs::uns), [0] adjoint on dst, [1] bound on src
+  DBuf tab[2];                // conv: conv_tables(plan[t], t)
 };
 
 struct NodeH {
@@ -575,6 +579,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
           fail(GCP_EUNSUPPORTED, "conv rows too wide for an LDS slab");
         E->plan[0] = conv_plan(E->cg, 0);
         E->plan[1] = conv_plan(E->cg, 1);
+        for (int t = 0; t < 2; ++t) E->tab[t].upload(conv_tables(E->plan[t], t));
         E->ldk_f = kf;
         E->ldk_t = kt;
         E->W32.upload(fw); E->W16.upload(to_bf16(fw));
@@ -1443,6 +1448,7 @@ void set_plan(const Call& c, int eid, ConvArgs& ca) {
   const EdgeH& E = *c.net->edges[eid];
   const int t = ca.trans;
   ca.plan = &E.plan[t];
+  ca.tab = E.tab[t].as<int32_t>();
   ca.uns = E.uns[t].as<int2>();
   ca.uns_off = E.uns_off[t].as<int32_t>();
   if (!c.cuts) return;

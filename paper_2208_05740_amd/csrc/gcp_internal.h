@@ -2,6 +2,8 @@
 // gfx950 kernels (kernels.hip).  Not part of the public ABI.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <vector>
 #include <stdint.h>
 
 namespace gcp {
@@ -185,6 +187,7 @@ struct ConvArgs {
   // unstable ones, and in a second list the other ones with cut entries
   const int2* uns; const int32_t* uns_off;
   const int2* cut; const int32_t* cut_off;
+  const int32_t* tab;     // conv_tables(*plan, trans)
   const ConvPlan* plan;   // host: conv_plan(cg, trans)
 };
 // Work split of one conv launch: the epilogue-side rows form bands of BH
@@ -205,6 +208,7 @@ struct ConvPlan {
 // four within 64 KB; slab_bytes (optional) gets that slab's size.
 bool conv_accepted(const ConvGeom& g, int trans, long* slab_bytes = nullptr);
 ConvPlan conv_plan(const ConvGeom& g, int trans);
+std::vector<int32_t> conv_tables(const ConvPlan& P, int trans);
 // conv weights laid out as the kernels read them (Bt above); raw is [co][ci][kh][kw]
 int conv_ldb(const ConvGeom& g, int trans);
 void conv_pack_weights(const ConvGeom& g, int trans, const float* raw, float* out);

@@ -415,7 +415,10 @@ __device__ __forceinline__ void sub_epilogue(const GemmArgs& g, const Epi& epi, 
     float sG[4], sH[4], sQ[4];
     tile_cuts(epi.a.cc, epi.a.rp, t, p, sG, sH, sQ);
     const float val[4] = {acc[0], acc[1], acc[2], acc[3]};
-    epi.tile(val, p, t, sG, sH, sQ, rs, g.partial != nullptr);
+    const NodeDev& nd = epi.col_node();
+    const uint32_t pitch = nd.ld * (uint32_t)sizeof(T), off = lane_off(t, t.jv, nd.ld, t.j, sizeof(T));
+    const RowWin w = row_win(epi.out_base(), t.m0, t.rows, pitch);
+    epi.tile(val, p, t, sG, sH, sQ, rs, g.partial != nullptr, [&](int q, T v) { win_st<T>(w, off + q * pitch, v); });
   } else {
     LaneCoords<4, 1, false> lc;
 #pragma unroll
