@@ -135,9 +135,9 @@ static void plan_bands(ConvPlan& P, int trans, int bh) {
 // base [KP], base (low half) and result offset (high half, 0xffff: none) of
 // each GEMM row [16 MT], phase of each 16-row tile [MT] and the number of
 // tiles.  Made by every workgroup, with their integer divisions, these were
-// part of what a workgroup costs apart from its data; with the lists' first
-// entries fetched ahead of the slab (band_epilogue) the ascent of the 3x32x32
-// ResNet, 4608 rows in bf16, went from 72.1 to 66.9 ms.
+// part of what a workgroup costs apart from its data: the ascent of the
+// 3x32x32 ResNet, 4608 rows in bf16, 72.1 -> 66.9 ms (with the lists walked as
+// one, by the dense layers' branch-free loads).
 __host__ __device__ static inline int table_words(const ConvPlan& P) { return P.KP + 16 * P.MT + (P.MT + 1 + 3) / 4 * 4; }
 std::vector<int32_t> conv_tables(const ConvPlan& P, int trans) {
   const int words = table_words(P);
@@ -675,39 +675,14 @@ struct BandList {
   __device__ inline int2 at(int i) const { return i < n_u ? uns[i] : cut[i - n_u]; }
 };
 
-// A thread's current list entry and what the epilogue reads for it.
-struct BandItem {
-  int2 e;
-  SubPre p;
-};
-template <typename T, class Epi>
-__device__ __forceinline__ TileLane band_lane(const ConvArgs& c, int r0, int j, bool has) {
-  return TileLane{r0, min(kRows, c.M - r0), 0, j, j, has};
-}
-// entry i (past the end: the last one, whose values are not used)
-template <typename T, class Epi>
-__device__ __forceinline__ void fetch_item(const ConvArgs& c, const Epi& epi, const BandList& l, int r0, int i, BandItem& it) {
-  if constexpr (BandOps<Epi>::kLists) {
-    if (l.n == 0) return;
-    it.e = l.at(min(i, l.n - 1));
-    it.p.kind = it.e.y;
-    it.p.rng = make_int2(0, 0);
-    const int2* rng = band_cuts(epi).rng;
-    if (rng) it.p.rng = rng[it.e.x];
-    if constexpr (Epi::kPre > 0) fetch_pre<T>(epi, band_lane<T, Epi>(c, r0, it.e.x, i < l.n), it.p);
-  }
-}
-
 // Fused epilogue of one workgroup's band over the results of its kRows batch
 // rows in LDS (cell n * OS + position of channel n; position (y - yb0) * We +
 // x), then the row constant of each batch row into its partial slot slot0 +
-// band.  it: this thread's first list entry, fetched before the GEMM so that
-// its loads (three round trips: entry, kind and cut range, alpha and moments)
-// arrive under the slab's.
+// band.  (A thread's first list entry fetched ahead of the slab measured the
+// same as here: two workgroups per CU cover these loads.)
 template <typename T, int NW, class Epi>
 __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan& P, const Epi& epi, float4* outs,
-                                              double* red, int r0, int band, int yb0, int yb1, const BandList& list,
-                                              BandItem& it) {
+                                              double* red, int r0, int band, int yb0, int yb1) {
   constexpr int NT = NW * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int HWe = P.He * P.We;
@@ -718,26 +693,32 @@ __device__ __forceinline__ void band_epilogue(const ConvArgs& c, const ConvPlan&
   for (int q = 0; q < kRows; ++q) rs[q] = 0.0;
   if constexpr (BandOps<Epi>::kLists) {
     const float inv_hw = 1.f / (float)HWe;
+    const BandList list(c, band);
+    const int2* rng = band_cuts(epi).rng;
     for (int i = tid; i < list.n; i += NT) {
-      if (i != tid) fetch_item<T>(c, epi, list, r0, i, it);
+      const int2 e = list.at(i);
       int off;
-      const int n = div_rem(it.e.x, HWe, inv_hw, &off);
+      const int n = div_rem(e.x, HWe, inv_hw, &off);
       float4& cell = outs[n * P.OS + off - j0];
       const float4 v = cell;
       if constexpr (Epi::kPre > 0) {
-        const TileLane t = band_lane<T, Epi>(c, r0, it.e.x, true);
+        const TileLane t{r0, min(kRows, c.M - r0), 0, e.x, e.x, true};
+        SubPre p;
+        p.kind = e.y;
+        p.rng = rng ? rng[e.x] : make_int2(0, 0);
+        fetch_pre<T>(epi, t, p);
         float sG[4], sH[4], sQ[4];
-        tile_cuts(epi.a.cc, epi.a.rp, t, it.p, sG, sH, sQ);
+        tile_cuts(epi.a.cc, epi.a.rp, t, p, sG, sH, sQ);
         const float val[4] = {v.x, v.y, v.z, v.w};
-        epi.tile(val, it.p, t, sG, sH, sQ, rs, c.partial != nullptr, [&](int q, T o) { ((float*)&cell)[q] = from_t<T>(o); });
+        epi.tile(val, p, t, sG, sH, sQ, rs, c.partial != nullptr, [&](int q, T o) { ((float*)&cell)[q] = from_t<T>(o); });
       } else {
         LaneCoords<kRows, 1, false> lc;
 #pragma unroll
         for (int q = 0; q < kRows; ++q) lc.r[q] = r0 + q;
-        lc.j[0][0] = it.e.x;
+        lc.j[0][0] = e.x;
         ColPre<1> pre;
-        pre.kind[0] = it.e.y;
-        pre.rng[0] = it.p.rng;
+        pre.kind[0] = e.y;
+        pre.rng[0] = rng ? rng[e.x] : make_int2(0, 0);
         const float val[1][kRows] = {{v.x, v.y, v.z, v.w}};
         BandOps<Epi>::run(epi, lc, pre, val, (float*)&cell, r0, c.M, size, rs);
       }
@@ -804,12 +785,7 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
   const int yb0 = band * P.BH, yb1 = min(P.He, yb0 + P.BH);
   const int sy0 = TRANS ? (yb0 + p) / s - (P.A - 1) : yb0 * s - p;   // source row of slab row 0
   const uint4* bt = (const uint4*)(c.tab + (size_t)band * words);
-  const uint4 t0 = bt[min(tid, words / 4 - 1)];        // (in flight with the list's loads)
-  const BandList list(c, band);
-  BandItem it;
-  fetch_item<T>(c, epi, list, r0, tid, it);
-  if (tid < words / 4) ((uint4*)koff)[tid] = t0;
-  for (int i = tid + NT; i < words / 4; i += NT) ((uint4*)koff)[i] = bt[i];
+  for (int i = tid; i < words / 4; i += NT) ((uint4*)koff)[i] = bt[i];
   const int nck = (P.Nch + 16 * TN - 1) / (16 * TN);
   const int g = lane >> 4;
   const int KR = (P.Kreal + KC - 1) / KC * KC;
@@ -891,7 +867,7 @@ __global__ void __launch_bounds__(NW * 64) conv_slab_kernel(ConvArgs c, ConvPlan
     }
   }
   __syncthreads();
-  band_epilogue<T, NW>(c, P, epi, outs, red, r0, band, yb0, yb1, list, it);
+  band_epilogue<T, NW>(c, P, epi, outs, red, r0, band, yb0, yb1);
 }
 
 // Transposed convolution into a source of at most four channels (the
@@ -974,10 +950,7 @@ __global__ void __launch_bounds__(kDirNW * 64) convT_direct_kernel(ConvArgs c, C
     for (int ch = 0; ch < NC; ++ch) *(f4*)(outs + ch * P.OS + coff) = acc[ch];
   }
   __syncthreads();
-  const BandList list(c, band);
-  BandItem it;
-  fetch_item<T>(c, epi, list, r0, tid, it);
-  band_epilogue<T, kDirNW>(c, P, epi, outs, red, r0, band, yb0, yb1, list, it);
+  band_epilogue<T, kDirNW>(c, P, epi, outs, red, r0, band, yb0, yb1);
 }
 
 // launch configurations: waves per workgroup x column tiles per wave
