@@ -28,6 +28,12 @@
 // 16-byte store.  The row constant of a band goes to one partial slot per
 // batch row: slot0 + band.
 //
+// What bounds them: a workgroup's phases (slab, products, lists, streaming)
+// follow one another and two workgroups per CU overlap them little, so their
+// times add up.  Against the form with one batch row at a time (RB = 1, below),
+// the CNN's kernels at 18432 rows in fp32: relaxation 670 -> 326 us, adjoint
+// 745 -> 437, adjoint from the sign matrix 706 -> 312.
+//
 // The earlier form (one batch row in the slab at a time, element gathers of 4
 // bytes, the full epilogue over every neuron) is kept as RB = 1 with the same
 // epilogue, for convolutions whose rows are too wide for four slabs.

@@ -89,8 +89,23 @@ static hipError_t launch_layer(const GemmLaunch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Bytes of one row of the widest array a tile addresses by 32-bit offsets; 0
+// for epilogues without them.
+template <class Epi, class Args>
+static long row_bytes(const Args& a) {
+  if constexpr (Epi::kPre > 0) return 4l * (a.nd.ld > a.rp.n_I ? a.nd.ld : a.rp.n_I);
+  else return 0;
+}
+
 template <typename T, bool SIGN, class Epi, class Args>
 static hipError_t launch_any(int cfg, const GemmLaunch& L, hipStream_t st) {
+  // offsets of a tile's rows stay below 2 GiB (kNoElem): beyond 8 million
+  // neurons a row, 16-row tiles
+  if (!L.d_gs) {
+    const long row = row_bytes<Epi>(*(const Args*)L.epi);
+    if (row * 64 >= 1l << 31) cfg = 7;
+    if (row * 16 >= 1l << 31) return hipErrorInvalidValue;
+  }
   switch (cfg) {
     case 0: case 3: return launch_layer<T, 2, 2, 2, 2, 0, SIGN, Epi, Args>(L, st);
     case 1: return launch_layer<T, 1, 1, 2, 2, kDepth<Epi>, SIGN, Epi, Args>(L, st);
