@@ -41,11 +41,11 @@ def conv_class_of(symbol):
     """Kernel-class name ('convT_bound.bf16.w4x1', 'conv_adj.bf16.sign.w4x1',
     'conv_adj_pi.bf16.w8x1', ...) of a conv_slab instantiation (waves x
     column tiles), or None."""
-    m = re.search(r"conv_slab_kernelI(DF16b|f)Li(\d+)ELi(\d+)ELb([01])ELb([01])ENS_\d+(\w+?Epi)", symbol)
+    m = re.search(r"conv_slab_kernelI(DF16b|f)Li(\d+)ELi(\d+)E(?:Li\d+E)?Lb([01])ELb([01])ENS_\d+(\w+?Epi)", symbol)
     if m:
         dt, nw, tn, tr, sg, epi = m.groups()
     else:
-        m = re.search(r"conv_slab_kernel<(float|__bf16), (\d+), (\d+), (true|false), (true|false), gcp::(\w+Epi)",
+        m = re.search(r"conv_slab_kernel<(float|__bf16), (\d+), (\d+),(?: \d+,)? (true|false), (true|false), gcp::(\w+Epi)",
                       symbol)
         if not m:
             return None
@@ -76,22 +76,25 @@ def direct_class_of(symbol):
 
 def class_of(symbol):
     """Library kernel-class name ('adj.bf16.t32x32', 'convT_bound.bf16.w4x1',
-    ...) of a gemm_epi, conv_slab or direct transposed-conv instantiation,
+    ...) of a layer, gemm_epi, conv_slab or direct transposed-conv instantiation,
     from its mangled or demangled symbol; None otherwise."""
     if "conv_slab_kernel" in symbol:
         return conv_class_of(symbol)
     if "convT_direct_kernel" in symbol:
         return direct_class_of(symbol)
-    m = re.search(r"gemm_epi_kernelI(DF16b|f)Li(\d+)ELi(\d+)ELi\d+ELi\d+ELi\d+ELb([01])ENS_\d+(\w+?Epi)", symbol)
-    if m:
-        dt, bm, bn, sg, epi = m.groups()
+    direct = ""
+    m = (re.search(r"layer_kernelI(DF16b|f)Li(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb([01])ENS_\d+(\w+?Epi)", symbol) or
+         re.search(r"layer_kernel<(float|__bf16), (\d+), (\d+), (\d+), (\d+), (\d+), (true|false), gcp::(\w+Epi)", symbol))
+    if m:      # 16x16 sub-tiles per wave, waves, K steps held ahead by a direct tile (0: staged)
+        dt, tm, tn, wm, wn, depth, sg, epi = m.groups()
+        bm, bn, direct = int(tm) * int(wm) * 16, int(tn) * int(wn) * 16, "d" if depth != "0" else ""
     else:
-        m = re.search(r"gemm_epi_kernel<(float|__bf16), (\d+), (\d+), \d+, \d+, \d+, (true|false), gcp::(\w+Epi)",
-                      symbol)
+        m = (re.search(r"gemm_epi_kernelI(DF16b|f)Li(\d+)ELi(\d+)ELi\d+ELi\d+ELi\d+ELb([01])ENS_\d+(\w+?Epi)", symbol) or
+             re.search(r"gemm_epi_kernel<(float|__bf16), (\d+), (\d+), \d+, \d+, \d+, (true|false), gcp::(\w+Epi)", symbol))
         if not m:
             return None
         dt, bm, bn, sg, epi = m.groups()
-        sg = "1" if sg == "true" else "0"
+    sg = "1" if sg in ("1", "true") else "0"
     kind = {v: k for k, v in EPI.items()}.get(epi)
     if kind is None:
         return None
@@ -100,7 +103,7 @@ def class_of(symbol):
     name = f"{kind}.{'bf16' if dt in ('DF16b', '__bf16') else 'fp32'}"
     if sg == "1":
         name += ".sign"
-    return name + f".t{bm}x{bn}"
+    return name + f".t{bm}x{bn}{direct}"
 
 
 def kernel_times(db):
