@@ -139,8 +139,69 @@ std::string cls_name(const char* kind, int bf16, int sign, int cfg) {
 // launcher instantiates those epilogues for the small tiles only).
 int pi_cfg(int cfg) { return (cfg == 6 || cfg == 7) ? cfg : 5; }
 
+// Device memory of one call that makes and drops whole networks: buffers are
+// cut from chunks that are kept until the call ends, zero-filled when they are
+// made and again by rewind(), which the caller runs once nothing of the
+// previous network is left, on the device or the host.  The intermediate
+// bounds of the CNN (three prefix networks) spent 5.7 of 9.7 ms in 133
+// allocations and frees; with the arena they take 5.9 ms.
+class CallArena {
+  struct Chunk { char* p; size_t bytes, used; };
+  std::vector<Chunk> chunks;
+  static constexpr size_t kChunk = (size_t)32 << 20, kAlign = 256;
+  static void clear(void* p, size_t n) {
+    hip_check(hipMemset(p, 0, n), "hipMemset");
+    hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
+  }
+ public:
+  CallArena() = default;
+  CallArena(const CallArena&) = delete;
+  CallArena& operator=(const CallArena&) = delete;
+  ~CallArena() {
+    (void)hipDeviceSynchronize();     // an error may have left work in flight
+    for (Chunk& c : chunks) (void)hipFree(c.p);
+  }
+  void* take(size_t n) {
+    n = (n + kAlign - 1) / kAlign * kAlign;
+    for (Chunk& c : chunks)
+      if (c.bytes - c.used >= n) {
+        void* q = c.p + c.used;
+        c.used += n;
+        return q;
+      }
+    Chunk c{nullptr, std::max(n, kChunk), n};
+    if (hipMalloc((void**)&c.p, c.bytes) != hipSuccess) {   // give back what this network does not use, ask for n alone
+      (void)hipGetLastError();
+      for (size_t i = chunks.size(); i-- > 0;)
+        if (chunks[i].used == 0) {
+          (void)hipFree(chunks[i].p);
+          chunks.erase(chunks.begin() + i);
+        }
+      c.bytes = n;
+      hip_check(hipMalloc((void**)&c.p, c.bytes), "hipMalloc");
+    }
+    chunks.push_back(c);
+    clear(c.p, c.bytes);
+    return c.p;
+  }
+  void rewind() {
+    for (Chunk& c : chunks) {
+      if (c.used) clear(c.p, c.used);
+      c.used = 0;
+    }
+  }
+};
+// The arena of the call this thread is in, if any (ArenaScope).
+thread_local CallArena* t_arena = nullptr;
+struct ArenaScope {
+  CallArena arena;
+  CallArena* outer = t_arena;
+  ArenaScope() { t_arena = &arena; }
+  ~ArenaScope() { t_arena = outer; }
+};
+
 // Owned device allocation (zero-filled at allocation), or a borrowed view of
-// memory owned elsewhere (never freed here).  The fill and uploads run on the
+// memory owned elsewhere (never freed here; a call's arena among them).  The fill and uploads run on the
 // null stream and are waited for before returning: callers' streams may be
 // non-blocking (no implicit order with the null stream), and their work on a
 // new buffer must not race its clear.  A free first waits for the device, as
@@ -180,6 +241,10 @@ struct DBuf {
   void alloc(size_t n) {
     release();
     if (n == 0) return;
+    if (t_arena) {
+      borrow(t_arena->take(n), n);
+      return;
+    }
     hip_check(hipMalloc(&p, n), "hipMalloc");
     bytes = n;
     hip_check(hipMemset(p, 0, n), "hipMemset");
@@ -192,8 +257,13 @@ struct DBuf {
   template <class T> void upload(const std::vector<T>& v) {
     release();
     if (v.empty()) return;
-    hip_check(hipMalloc(&p, v.size() * sizeof(T)), "hipMalloc");
-    bytes = v.size() * sizeof(T);
+    const size_t n = v.size() * sizeof(T);
+    if (t_arena) {
+      borrow(t_arena->take(n), n);
+    } else {
+      hip_check(hipMalloc(&p, n), "hipMalloc");
+      bytes = n;
+    }
     hip_check(hipMemcpy(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice), "hipMemcpy");
     hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
   }
@@ -3281,6 +3351,7 @@ extern "C" int gcp_crown_bounds_domain(const gcp_net_desc* desc, const double* x
     if (split_sign[s] != 1 && split_sign[s] != -1) fail(GCP_EINVAL, "split sign must be +1 or -1");
     if (!seen.insert({k, split_neuron[s]}).second) fail(GCP_EINVAL, "neuron split twice");
   }
+  ArenaScope scope;
   std::vector<std::vector<double>> L(out), U(out);
   std::vector<gcp_node_desc> nodes(desc->nodes, desc->nodes + desc->n_nodes);
   constexpr int kRowsPerCall = 4096;
@@ -3289,6 +3360,7 @@ extern "C" int gcp_crown_bounds_domain(const gcp_net_desc* desc, const double* x
     const int d = nk.c * nk.h * nk.w;
     if (d <= 0) fail(GCP_EINVAL, "bad node shape");
     if (!lower[k] || !upper[k]) fail(GCP_EINVAL, "null bound output of node " + std::to_string(k));
+    if (k > 0) scope.arena.rewind();    // (the last bounds of node k - 1 were waited for)
     // the prefix network: nodes 0..k with node k as its output (the
     // pre-activation), earlier nodes carrying the bounds found so far
     gcp_net_desc sub{desc->in_c, desc->in_h, desc->in_w, k + 1, nodes.data()};
