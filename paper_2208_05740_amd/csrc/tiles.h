@@ -611,31 +611,60 @@ __device__ __forceinline__ void bound_elem_rows(const float* bcast, const void* 
   const int j = cb * 256 + tx;
   const int M = a.rp.M;
   BoundEpi<T, PI> epi{a};
-  LaneCoords<R, 1, false> lc;
-#pragma unroll
-  for (int q = 0; q < R; ++q) lc.r[q] = r0 + q;
-  lc.j[0][0] = j;
-  float val[1][R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    const int r = r0 + q;
-    float pre = 0.f;
-    if (j < a.nd.size && r < M) {
-      if (bcast) pre += bcast[(size_t)(r % a.rp.S) * a.nd.ld + j];
-      if (src) pre += from_t<T>(((const T*)src)[(size_t)r * a.nd.ld + j]);
-    }
-    val[0][q] = pre;
-  }
   double rs[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) rs[q] = 0.0;
-  typename BoundEpi<T, PI>::template Frag<R, 1, false> fr;
-  epi.template load<R, 1, false>(fr, lc, M, a.nd.size);
-  if (!partial) {            // the row constants are not asked for: rs is dead here
+  if constexpr (!PI && !OPAQUE) {
+    // as a layer tile of one column per lane (r0 is wave-uniform): bound by the
+    // wave's instructions and its alpha and cut loads; with 64-bit addresses
+    // and a division per row, 784-256x6 MLP: 9 rows 4.3 -> 3.4 us, 9216 rows
+    // 16.2 -> 14.2, 36864 rows 53.6 -> 42.4
+    static_assert(R == 4, "four rows, as BoundEpi::tile takes them");
+    const TileLane t{r0, min(R, M - r0), 0, j, min(j, a.nd.size - 1), j < a.nd.size};
+    SubPre p;
+    fetch_words(epi, j, a.nd.size, p);
+    const uint32_t pB = a.nd.ld * 4u, pT = a.nd.ld * (uint32_t)sizeof(T), oT = lane_off(t, t.jv, a.nd.ld, j, sizeof(T));
+    const RowWin ws = row_win(src, r0, t.rows, pT);
+    const uint32_t oB = lane_off(t, t.jv, a.nd.ld, j, 4);
+    float val[R];
+    int s = r0 % a.rp.S;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      val[q] = 0.f;
+      if (bcast) val[q] += win_ld<float>(row_win(bcast, s, 1, pB), oB);
+      if (src) val[q] += from_t<T>(win_ld<T>(ws, oT + q * pT));
+      s = s + 1 == a.rp.S ? 0 : s + 1;
+    }
+    fetch_pre<T>(epi, t, p);
+    float sG[R], sH[R], sQ[R];
+    tile_cuts(a.cc, a.rp, t, p, sG, sH, sQ);
+    const RowWin w = row_win(a.lam_out, r0, t.rows, pT);
+    epi.tile(val, p, t, sG, sH, sQ, rs, partial != nullptr, [&](int q, T v) { win_st<T>(w, oT + q * pT, v); });
+    if (!partial) return;      // the row constants are not asked for
+  } else {
+    LaneCoords<R, 1, false> lc;
+#pragma unroll
+    for (int q = 0; q < R; ++q) lc.r[q] = r0 + q;
+    lc.j[0][0] = j;
+    float val[1][R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int r = r0 + q;
+      float pre = 0.f;
+      if (j < a.nd.size && r < M) {
+        if (bcast) pre += bcast[(size_t)(r % a.rp.S) * a.nd.ld + j];
+        if (src) pre += from_t<T>(((const T*)src)[(size_t)r * a.nd.ld + j]);
+      }
+      val[0][q] = pre;
+    }
+    typename BoundEpi<T, PI>::template Frag<R, 1, false> fr;
+    epi.template load<R, 1, false>(fr, lc, M, a.nd.size);
+    if (!partial) {            // the row constants are not asked for: rs is dead here
+      epi.template apply<R, 1, false>(fr, lc, val, rs, M, a.nd.size);
+      return;
+    }
     epi.template apply<R, 1, false>(fr, lc, val, rs, M, a.nd.size);
-    return;
   }
-  epi.template apply<R, 1, false>(fr, lc, val, rs, M, a.nd.size);
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const double t = wave_sum64(rs[q]);
