@@ -212,8 +212,7 @@ static long slab_cells(const ConvPlan& P) { return (long)P.Kch * P.CHS; }
 static long out_cells(const ConvPlan& P) { return (long)P.Nch * P.OS; }
 static int plan_items(const ConvPlan& P) { return P.MT * ((P.Nch + 15) / 16); }
 
-// The plan that holds one batch row in the slab: it fits whenever a conv is
-// accepted at all (conv_accepted).
+// The plan that holds one batch row in the slab.
 static ConvPlan conv_plan_row(const ConvGeom& g, int trans) {
   ConvPlan P = plan_dims(g, trans);
   auto bytes_for = [&](int bh) {
@@ -250,14 +249,10 @@ ConvPlan conv_plan(const ConvGeom& g, int trans) {
   return conv_plan_row(g, trans);
 }
 
-bool conv_accepted(const ConvGeom& g, int trans, long* slab_bytes) {
+long conv_row_slab(const ConvGeom& g, int trans) {
   const ConvPlan P = conv_plan_row(g, trans);
   const long rows = trans ? (P.BH - 1) / P.s + 1 + P.A : P.rows_max;
-  const long slab = (long)P.Kch * rows * P.Wp * 4;
-  if (slab_bytes) *slab_bytes = slab;
-  const long lds = align16(P.KP * 4) + 256 + align16(P.MT * 4) + P.MT * 16 * 8 + (slab + 15) / 16 * 16 +
-                   (long)kRows * align16((int)out_cells(P) * 4);
-  return lds <= kRowLds;
+  return (long)P.Kch * rows * P.Wp * 4;
 }
 
 int conv_ldb(const ConvGeom& g, int trans) { return plan_dims(g, trans).KP; }
@@ -303,6 +298,15 @@ static int conv_lds_bytes(const ConvPlan& P, int esz, int nw, bool alias) {
   const int slab = align16(P.rb * (int)slab_cells(P) * esz), outs = align16((int)out_cells(P) * 16);
   return align16(nw * 8 * kRows) + table_words(P) * 4 +
          (alias ? std::max(slab, outs) : slab + outs);
+}
+
+// What a launch takes (every shape of workgroup asks for at most this much):
+// its LDS within a workgroup's, at the operand's size, and the slab and result
+// offsets in the halves of a descriptor (conv_tables).
+bool conv_fits(const ConvPlan& P, int bf16) {
+  const bool alias = conv_alias(P, 8, 1);
+  return conv_lds_bytes(P, bf16 ? 2 : 4, P.rb == 1 ? 4 : 8, alias) <= kLdsLimit && P.CHS < 0xffff &&
+         P.BH * P.We < 0xffff;
 }
 
 // ---------------------------------------------------------------- slab fill
@@ -981,7 +985,7 @@ static hipError_t conv_go(const ConvArgs& c, const ConvPlan& P, const Epi& epi, 
 template <typename T, bool TRANS, bool SIGN, class Epi>
 static hipError_t conv_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;
-  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
+  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_fits(P, sizeof(T) == 2)) return hipErrorInvalidValue;
   if (P.rb == 1) return conv_go<T, 4, 1, 1, TRANS, SIGN>(c, P, epi, st);
   if (cfg >= 0 && cfg < conv_num_configs() && !conv_alias(P, kConv[cfg].nw, kConv[cfg].tn)) cfg = 2;
   switch (cfg) {
@@ -1019,7 +1023,7 @@ static hipError_t conv_typed(int cfg, EpiKind kind, const ConvArgs& c, const voi
 template <typename T, bool TRANS, bool SIGN, class Epi>
 static hipError_t conv_pi_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;
-  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_accepted(c.cg, TRANS ? 1 : 0)) return hipErrorInvalidValue;
+  if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_fits(P, sizeof(T) == 2)) return hipErrorInvalidValue;
   if (P.rb == 1) return conv_go<T, 4, 1, 1, TRANS, SIGN>(c, P, epi, st);
   if (cfg == 0 && conv_alias(P, 4, 1)) return conv_go<T, 4, 1, 4, TRANS, SIGN>(c, P, epi, st);
   return conv_go<T, 8, 1, 4, TRANS, SIGN>(c, P, epi, st);

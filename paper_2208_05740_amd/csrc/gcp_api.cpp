@@ -642,10 +642,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
         std::vector<float> fw((size_t)n.c * kf), ft((size_t)nph * ci * kt);
         conv_pack_weights(E->cg, 0, raw.data(), fw.data());
         conv_pack_weights(E->cg, 1, raw.data(), ft.data());
-        long slab_f = 0, slab_t = 0;
-        conv_accepted(E->cg, 0, &slab_f);
-        conv_accepted(E->cg, 1, &slab_t);
-        if (slab_f > 48 * 1024 || slab_t > 48 * 1024)
+        if (conv_row_slab(E->cg, 0) > 48 * 1024 || conv_row_slab(E->cg, 1) > 48 * 1024)
           fail(GCP_EUNSUPPORTED, "conv rows too wide for an LDS slab");
         E->plan[0] = conv_plan(E->cg, 0);
         E->plan[1] = conv_plan(E->cg, 1);

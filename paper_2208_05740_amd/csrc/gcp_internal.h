@@ -204,10 +204,12 @@ struct ConvPlan {
   int MT;                         // most 16-row GEMM tiles in one band (phases padded to 16 rows)
   int rb;                         // batch rows in the slab at once: 4, or 1 where four do not fit
 };
-// Whether a launch takes the conv: a slab of one batch row and the results of
-// four within 64 KB; slab_bytes (optional) gets that slab's size.
-bool conv_accepted(const ConvGeom& g, int trans, long* slab_bytes = nullptr);
+// Bytes of the slab that holds one batch row in fp32, in bands as high as it
+// allows: a net is created if it has at most 48 KB, in both directions.
+long conv_row_slab(const ConvGeom& g, int trans);
 ConvPlan conv_plan(const ConvGeom& g, int trans);
+// whether launch_conv takes the plan, in every shape of workgroup
+bool conv_fits(const ConvPlan& P, int bf16);
 std::vector<int32_t> conv_tables(const ConvPlan& P, int trans);
 // conv weights laid out as the kernels read them (Bt above); raw is [co][ci][kh][kw]
 int conv_ldb(const ConvGeom& g, int trans);
