@@ -212,6 +212,27 @@ static long slab_cells(const ConvPlan& P) { return (long)P.Kch * P.CHS; }
 static long out_cells(const ConvPlan& P) { return (long)P.Nch * P.OS; }
 static int plan_items(const ConvPlan& P) { return P.MT * ((P.Nch + 15) / 16); }
 
+// Whether a launch of nw waves and tn column tiles per wave holds every item
+// of a band in its accumulators, so that the results may replace the slab.
+static bool conv_alias(const ConvPlan& P, int nw, int tn) {
+  return P.rb == 4 && P.MT * ((P.Nch + 16 * tn - 1) / (16 * tn)) <= nw * kIT;
+}
+
+static int conv_lds_bytes(const ConvPlan& P, int esz, int nw, bool alias) {
+  const int slab = align16(P.rb * (int)slab_cells(P) * esz), outs = align16((int)out_cells(P) * 16);
+  return align16(nw * 8 * kRows) + table_words(P) * 4 +
+         (alias ? std::max(slab, outs) : slab + outs);
+}
+
+// What a launch takes (every shape of workgroup asks for at most this much):
+// its LDS within a workgroup's, at the operand's size, and the slab and result
+// offsets in the halves of a descriptor (conv_tables).
+bool conv_fits(const ConvPlan& P, int bf16) {
+  const bool alias = conv_alias(P, 8, 1);
+  return conv_lds_bytes(P, bf16 ? 2 : 4, P.rb == 1 ? 4 : 8, alias) <= kLdsLimit && P.CHS < 0xffff &&
+         P.BH * P.We < 0xffff;
+}
+
 // The plan that holds one batch row in the slab.
 static ConvPlan conv_plan_row(const ConvGeom& g, int trans) {
   ConvPlan P = plan_dims(g, trans);
@@ -228,24 +249,29 @@ static ConvPlan conv_plan_row(const ConvGeom& g, int trans) {
 
 // Bands as high as fit (a higher band re-reads fewer halo rows) with the
 // slab of four batch rows within the budget of two workgroups per CU, then
-// one, and its accumulators within two items per wave.
-ConvPlan conv_plan(const ConvGeom& g, int trans) {
+// one, and its accumulators within two items per wave.  The budgets count four
+// bytes an element for either operand type, so that both run the same bands;
+// what a launch asks for beside the slab or the results, the tables above all
+// (four bytes per K index), may still not fit: 320 -> 64 channels of 3x3 at
+// 8x8 are 150 KB of slab and 11.8 KB of tables in fp32, which takes another
+// plan, and half that slab in bf16, which keeps this one.
+ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16) {
   ConvPlan P = plan_dims(g, trans);
   P.rb = 4;
   if (trans && P.Nch <= 4 && direct_shape(P))   // bands of the direct kernel: one 64-position chunk per wave
     for (int bh = P.He; bh >= 1; --bh) {
       plan_bands(P, trans, bh);
       if (direct_chunks(P) <= kDirNW && plan_items(P) <= kItems &&
-          16 * std::max(slab_cells(P), out_cells(P)) <= kSlabBudget[1])
+          16 * std::max(slab_cells(P), out_cells(P)) <= kSlabBudget[1] && conv_fits(P, bf16))
         return P;
     }
   for (long budget : kSlabBudget)
     for (int bh = P.He; bh >= 1; --bh) {
       plan_bands(P, trans, bh);
-      if (plan_items(P) <= kItems && 16 * std::max(slab_cells(P), out_cells(P)) <= budget) return P;
+      if (plan_items(P) <= kItems && 16 * std::max(slab_cells(P), out_cells(P)) <= budget && conv_fits(P, bf16)) return P;
     }
   plan_bands(P, trans, 1);   // more channels or positions than the waves hold: results beside the slab
-  if (16 * (slab_cells(P) + out_cells(P)) <= kSlabBudget[1]) return P;
+  if (16 * (slab_cells(P) + out_cells(P)) <= kSlabBudget[1] && conv_fits(P, bf16)) return P;
   return conv_plan_row(g, trans);
 }
 
@@ -286,27 +312,6 @@ void conv_pack_weights(const ConvGeom& g, int trans, const float* raw, float* ou
         out[((size_t)ph * g.ci + c) * ldb + k] = v;
       }
   }
-}
-
-// Whether a launch of nw waves and tn column tiles per wave holds every item
-// of a band in its accumulators, so that the results may replace the slab.
-static bool conv_alias(const ConvPlan& P, int nw, int tn) {
-  return P.rb == 4 && P.MT * ((P.Nch + 16 * tn - 1) / (16 * tn)) <= nw * kIT;
-}
-
-static int conv_lds_bytes(const ConvPlan& P, int esz, int nw, bool alias) {
-  const int slab = align16(P.rb * (int)slab_cells(P) * esz), outs = align16((int)out_cells(P) * 16);
-  return align16(nw * 8 * kRows) + table_words(P) * 4 +
-         (alias ? std::max(slab, outs) : slab + outs);
-}
-
-// What a launch takes (every shape of workgroup asks for at most this much):
-// its LDS within a workgroup's, at the operand's size, and the slab and result
-// offsets in the halves of a descriptor (conv_tables).
-bool conv_fits(const ConvPlan& P, int bf16) {
-  const bool alias = conv_alias(P, 8, 1);
-  return conv_lds_bytes(P, bf16 ? 2 : 4, P.rb == 1 ? 4 : 8, alias) <= kLdsLimit && P.CHS < 0xffff &&
-         P.BH * P.We < 0xffff;
 }
 
 // ---------------------------------------------------------------- slab fill
@@ -981,7 +986,7 @@ static hipError_t conv_go(const ConvArgs& c, const ConvPlan& P, const Epi& epi, 
 }
 
 // Configurations that cannot hold the band's accumulators run as 8 waves x 1
-// column tile, whose plan always fits.
+// column tile.
 template <typename T, bool TRANS, bool SIGN, class Epi>
 static hipError_t conv_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;

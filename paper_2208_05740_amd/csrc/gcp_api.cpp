@@ -284,6 +284,14 @@ struct PersistPlan {
   double bytes = 0.0, alg = 0.0, flops = 0.0;   // per iteration, both byte models and the GEMM FLOPs
 };
 
+// A conv edge in one direction ([0] adjoint, lists of dst's neurons; [1]
+// bound, of src's) and operand type.
+struct ConvSide {
+  ConvPlan plan;
+  DBuf tab;            // conv_tables(plan, direction)
+  DBuf uns, uns_off;   // unstable neurons band by band (ConvArgs::uns)
+};
+
 struct EdgeH {
   int src, dst, kind;
   int kh = 0, kw = 0, stride = 1, pad = 0;
@@ -296,9 +304,9 @@ struct EdgeH {
   DBuf WT16f;    // conv: WT16's values as fp32 (read by the direct transposed conv in bf16 mode)
   DBuf Wraw;     // dense [d_dst][d_src] unpadded fp32 (for c-hat and W x0); conv: [co][ci][kh][kw]
   int ldk_f = 0, ldk_t = 0;   // conv: padded K of W32/W16 (adjoint) and WT32/WT16 (bound)
-  ConvPlan plan[2];           // conv: conv_plan(cg, trans)
-  DBuf uns[2], uns_off[2];    // conv: unstable neurons band by band (ConvArgs::uns), [0] adjoint on dst, [1] bound on src
-  DBuf tab[2];                // conv: conv_tables(plan[t], t)
+  ConvSide side[2][2];        // conv: by direction and operand type; bf16 mostly runs fp32's plan and
+  int n_side[2] = {1, 1};     // has one of its own only where that differs
+  int side_of(int t, int bf16) const { return bf16 ? n_side[t] - 1 : 0; }
 };
 
 struct NodeH {
@@ -386,7 +394,7 @@ struct gcp_cuts {
   std::vector<Col> cols;   // per node; index n_nodes is the network input
   // per conv edge and direction (as EdgeH::uns): neurons without an alpha
   // that have entries, band by band (ConvArgs::cut); null buffers if none
-  struct EdgeList { DBuf ent[2], off[2]; };
+  struct EdgeList { DBuf ent[2][2], off[2][2]; };
   std::map<int, EdgeList> edge_lists;
   std::vector<int> nnz_node;   // merged entries per node (same indexing)
   // outward rounding: fp64 [3][N] = sum |coef| range over a cut's node
@@ -644,9 +652,14 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
         conv_pack_weights(E->cg, 1, raw.data(), ft.data());
         if (conv_row_slab(E->cg, 0) > 48 * 1024 || conv_row_slab(E->cg, 1) > 48 * 1024)
           fail(GCP_EUNSUPPORTED, "conv rows too wide for an LDS slab");
-        E->plan[0] = conv_plan(E->cg, 0);
-        E->plan[1] = conv_plan(E->cg, 1);
-        for (int t = 0; t < 2; ++t) E->tab[t].upload(conv_tables(E->plan[t], t));
+        for (int t = 0; t < 2; ++t) {
+          const ConvPlan p32 = conv_plan(E->cg, t, 0), p16 = conv_plan(E->cg, t, 1);
+          E->n_side[t] = p32.BH == p16.BH && p32.rb == p16.rb ? 1 : 2;
+          for (int b = 0; b < E->n_side[t]; ++b) {
+            E->side[t][b].plan = b ? p16 : p32;
+            E->side[t][b].tab.upload(conv_tables(E->side[t][b].plan, t));
+          }
+        }
         E->ldk_f = kf;
         E->ldk_t = kt;
         E->W32.upload(fw); E->W16.upload(to_bf16(fw));
@@ -676,10 +689,12 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
             if (t.rank_h[j] >= 0) u.push_back(j);
           return u;
         };
-        if (n.relu) upload_band_list(E->plan[0], unstable_of(n), &n.kind_h, E->uns[0], E->uns_off[0]);
-        if (ed.src >= 0) {
-          const NodeH& sn = net->nodes[ed.src];
-          upload_band_list(E->plan[1], unstable_of(sn), &sn.kind_h, E->uns[1], E->uns_off[1]);
+        for (int t = 0; t < 2; ++t) {
+          const NodeH* ln = t ? (ed.src >= 0 ? &net->nodes[ed.src] : nullptr) : (n.relu ? &n : nullptr);
+          for (int b = 0; ln && b < E->n_side[t]; ++b) {
+            ConvSide& sd = E->side[t][b];
+            upload_band_list(sd.plan, unstable_of(*ln), &ln->kind_h, sd.uns, sd.uns_off);
+          }
         }
       } else if (ed.kind == GCP_EDGE_IDENTITY) {
         if (E->d_src != E->d_dst) fail(GCP_EINVAL, "identity edge between different sizes");
@@ -1047,8 +1062,11 @@ extern "C" int gcp_cuts_create(const gcp_net* net, int32_t n_cuts, int64_t nnz, 
       const EdgeH& E = *net->edges[e];
       if (E.kind != GCP_EDGE_CONV) continue;
       const std::vector<int32_t>* kind = nd < 0 ? nullptr : &net->nodes[nd].kind_h;
-      if (E.dst == nd) upload_band_list(E.plan[0], other, kind, C->edge_lists[e].ent[0], C->edge_lists[e].off[0]);
-      if (E.src == nd) upload_band_list(E.plan[1], other, kind, C->edge_lists[e].ent[1], C->edge_lists[e].off[1]);
+      for (int t = 0; t < 2; ++t) {
+        if ((t ? E.src : E.dst) != nd) continue;
+        gcp_cuts::EdgeList& L = C->edge_lists[e];
+        for (int b = 0; b < E.n_side[t]; ++b) upload_band_list(E.side[t][b].plan, other, kind, L.ent[t][b], L.off[t][b]);
+      }
     }
   }
   *out = C.release();
@@ -1511,18 +1529,19 @@ void no_record(const Call& c, const char* what) {
 }
 
 // the plan and the band lists of a conv launch through edge eid (see ConvArgs)
-void set_plan(const Call& c, int eid, ConvArgs& ca) {
+void set_plan(const Call& c, int bf16, int eid, ConvArgs& ca) {
   const EdgeH& E = *c.net->edges[eid];
-  const int t = ca.trans;
-  ca.plan = &E.plan[t];
-  ca.tab = E.tab[t].as<int32_t>();
-  ca.uns = E.uns[t].as<int2>();
-  ca.uns_off = E.uns_off[t].as<int32_t>();
+  const int t = ca.trans, b = E.side_of(t, bf16);
+  const ConvSide& sd = E.side[t][b];
+  ca.plan = &sd.plan;
+  ca.tab = sd.tab.as<int32_t>();
+  ca.uns = sd.uns.as<int2>();
+  ca.uns_off = sd.uns_off.as<int32_t>();
   if (!c.cuts) return;
   auto it = c.cuts->edge_lists.find(eid);
   if (it == c.cuts->edge_lists.end()) return;
-  ca.cut = it->second.ent[t].as<int2>();
-  ca.cut_off = it->second.off[t].as<int32_t>();
+  ca.cut = it->second.ent[t][b].as<int2>();
+  ca.cut_off = it->second.off[t][b].as<int32_t>();
 }
 
 const void* wt_bound(const EdgeH& E, int bf16) { return bf16 ? E.WT16.p : E.WT32.p; }
@@ -1772,7 +1791,7 @@ struct BoundPass {
       ca.Bt = bf16 ? E.WT16.p : E.WT32.p; ca.ldb = E.ldk_t;
       ca.Btf = (const float*)(bf16 ? E.WT16f.p : E.WT32.p);
       ca.mp = c.rp.mp; ca.partial = nullptr;
-      set_plan(c, eid, ca);
+      set_plan(c, bf16, eid, ca);
       const double M = c.M, esz = bf16 ? 2 : 4;
       // every multiply-add of the forward conv appears once in its transpose
       const double flops = 2.0 * M * cg.ho * cg.wo * cg.ci * cg.co * cg.kh * cg.kw;
@@ -1792,7 +1811,7 @@ struct BoundPass {
         }
         return;
       }
-      const int nslot = E.plan[1].n_bands;   // row-partial slots: one per band
+      const int nslot = ca.plan->n_bands;   // row-partial slots: one per band
       if (p >= 0) {
         BoundEpiArgs a = bound_args(p, has_acc);
         if (!dry) {
@@ -1817,7 +1836,7 @@ struct BoundPass {
         a.contrib = want_contrib ? ws.contrib.as<float>() : nullptr;
         a.nnz_e = c.nnz;
         if (!dry) {
-          int cfg = choose_cfg("convT", EPI_CONC, bf16, 0, c.M, d_src, dn.size, c.st, conc_conv_cands(cg, E.plan[1]),
+          int cfg = choose_cfg("convT", EPI_CONC, bf16, 0, c.M, d_src, dn.size, c.st, conc_conv_cands(cg, *ca.plan),
                                [&](int cf) { return launch_conv(bf16, cf, EPI_CONC, ca, &a, c.st); });
           ConvArgs cr = ca;
           cr.partial = partial(); cr.slot0 = slot;
@@ -1937,7 +1956,7 @@ struct AdjPass {
       ca.Bt = bf16 ? E.WT16.p : E.WT32.p; ca.ldb = E.ldk_t;
       ca.Btf = (const float*)(bf16 ? E.WT16f.p : E.WT32.p);
       ca.mp = c.rp.mp; ca.partial = nullptr;
-      set_plan(c, n.consumers[0], ca);
+      set_plan(c, bf16, n.consumers[0], ca);
       const ConvGeom& cg = E.cg;
       const int cfg = choose_cfg("convT", EPI_BOUND, bf16, 0, c.M, E.d_src, dn.size, c.st, conv_cands(),
                                  [&](int cf) { return launch_conv(bf16, cf, EPI_AHAT, ca, &a, c.st); });
@@ -2028,7 +2047,7 @@ struct AdjPass {
         ca.X = A; ca.ldx = lda; ca.x_is_sign = sign;
         ca.Bt = bf16 ? E.W16.p : E.W32.p; ca.ldb = E.ldk_f;
         ca.mp = c.rp.mp; ca.partial = nullptr;
-        set_plan(c, order[q], ca);
+        set_plan(c, bf16, order[q], ca);
         const int HW = E.cg.ho * E.cg.wo;
         const double flops = 2.0 * M * HW * E.cg.co * E.cg.ci * E.cg.kh * E.cg.kw;
         const double wbytes = (double)E.cg.co * E.ldk_f * esz;

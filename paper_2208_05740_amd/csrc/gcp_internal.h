@@ -188,7 +188,7 @@ struct ConvArgs {
   const int2* uns; const int32_t* uns_off;
   const int2* cut; const int32_t* cut_off;
   const int32_t* tab;     // conv_tables(*plan, trans)
-  const ConvPlan* plan;   // host: conv_plan(cg, trans)
+  const ConvPlan* plan;   // host: conv_plan(cg, trans, bf16)
 };
 // Work split of one conv launch: the epilogue-side rows form bands of BH
 // rows; one workgroup takes four batch rows and one band: it stages the
@@ -207,7 +207,7 @@ struct ConvPlan {
 // Bytes of the slab that holds one batch row in fp32, in bands as high as it
 // allows: a net is created if it has at most 48 KB, in both directions.
 long conv_row_slab(const ConvGeom& g, int trans);
-ConvPlan conv_plan(const ConvGeom& g, int trans);
+ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16);
 // whether launch_conv takes the plan, in every shape of workgroup
 bool conv_fits(const ConvPlan& P, int bf16);
 std::vector<int32_t> conv_tables(const ConvPlan& P, int trans);

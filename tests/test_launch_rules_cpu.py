@@ -101,7 +101,7 @@ int main() {
 
 
 def _conv_sweep(tmp_path):
-    *cases, last = _run(tmp_path, CONV_SWEEP.replace("PLAN_FITS", "conv_fits(conv_plan(g, t), bf16)"))
+    *cases, last = _run(tmp_path, CONV_SWEEP.replace("PLAN_FITS", "conv_fits(conv_plan(g, t, bf16), bf16)"))
     words = last.split()
     taken, lost = [int(x) for x in words[1:3]], [int(x) for x in words[4:6]]
     assert min(taken) > 50000, last
@@ -111,3 +111,8 @@ def _conv_sweep(tmp_path):
 def test_bf16_convs_that_one_row_slabs_took_are_taken(tmp_path):
     lost, cases = _conv_sweep(tmp_path)
     assert lost[1] == 0, (lost, [c for c in cases if "bf16=1" in c][:10])
+
+
+def test_fp32_convs_that_one_row_slabs_took_are_taken(tmp_path):
+    lost, cases = _conv_sweep(tmp_path)
+    assert lost[0] == 0, (lost, cases[:10])
