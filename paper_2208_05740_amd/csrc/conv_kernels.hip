@@ -672,6 +672,13 @@ template <> struct BandOps<ConcEpi> {
   }
 };
 
+// An epilogue by its 64-bit form (arrays too large for the windows of
+// fetch_pre: windows_wide).
+template <class E> struct Wide : E {
+  static constexpr int kPre = 0;
+};
+template <class E> struct BandOps<Wide<E>> : BandOps<E> {};
+
 template <class Epi>
 __device__ inline const CutCol& band_cuts(const Epi& e) { return e.a.cc; }
 
@@ -1023,10 +1030,11 @@ static hipError_t conv_typed(int cfg, EpiKind kind, const ConvArgs& c, const voi
   }
 }
 
-// Explicit-pi epilogues (rho set): instantiated for one column tile per
-// wave only, 4 or 8 waves; the other shapes run as 8 waves.
+// Explicit-pi epilogues (rho set) and those with 64-bit addresses:
+// instantiated for one column tile per wave only, 4 or 8 waves; the other
+// shapes run as 8 waves.
 template <typename T, bool TRANS, bool SIGN, class Epi>
-static hipError_t conv_pi_any(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
+static hipError_t conv_few(int cfg, const ConvArgs& c, const Epi& epi, hipStream_t st) {
   const ConvPlan& P = *c.plan;
   if (!c.tab || c.ldb < P.KP || c.ldb % 32 != 0 || !conv_fits(P, sizeof(T) == 2)) return hipErrorInvalidValue;
   if (P.rb == 1) return conv_go<T, 4, 1, 1, TRANS, SIGN>(c, P, epi, st);
@@ -1035,13 +1043,23 @@ static hipError_t conv_pi_any(int cfg, const ConvArgs& c, const Epi& epi, hipStr
 }
 
 template <typename T>
-static hipError_t conv_typed_pi(int cfg, EpiKind kind, const ConvArgs& c, const void* epi, hipStream_t st) {
+static hipError_t conv_typed_wide(int cfg, EpiKind kind, const ConvArgs& c, const void* epi, hipStream_t st) {
   if (c.trans)
-    return kind == EPI_BOUND ? conv_pi_any<T, true, false>(cfg, c, BoundEpi<T, true>{*(const BoundEpiArgs*)epi}, st)
+    return kind == EPI_BOUND ? conv_few<T, true, false>(cfg, c, Wide<BoundEpi<T>>{{*(const BoundEpiArgs*)epi}}, st)
                              : hipErrorInvalidValue;
   if (kind != EPI_ADJ) return hipErrorInvalidValue;
-  if (c.x_is_sign) return conv_pi_any<T, false, true>(cfg, c, AdjEpi<T, true>{*(const AdjEpiArgs*)epi}, st);
-  return conv_pi_any<T, false, false>(cfg, c, AdjEpi<T, true>{*(const AdjEpiArgs*)epi}, st);
+  const Wide<AdjEpi<T>> e{{*(const AdjEpiArgs*)epi}};
+  return c.x_is_sign ? conv_few<T, false, true>(cfg, c, e, st) : conv_few<T, false, false>(cfg, c, e, st);
+}
+
+template <typename T>
+static hipError_t conv_typed_pi(int cfg, EpiKind kind, const ConvArgs& c, const void* epi, hipStream_t st) {
+  if (c.trans)
+    return kind == EPI_BOUND ? conv_few<T, true, false>(cfg, c, BoundEpi<T, true>{*(const BoundEpiArgs*)epi}, st)
+                             : hipErrorInvalidValue;
+  if (kind != EPI_ADJ) return hipErrorInvalidValue;
+  if (c.x_is_sign) return conv_few<T, false, true>(cfg, c, AdjEpi<T, true>{*(const AdjEpiArgs*)epi}, st);
+  return conv_few<T, false, false>(cfg, c, AdjEpi<T, true>{*(const AdjEpiArgs*)epi}, st);
 }
 
 bool conv_direct_ok(const ConvGeom& g, const ConvPlan& P, EpiKind kind) {
@@ -1086,9 +1104,11 @@ hipError_t launch_conv(int bf16_mode, int cfg, EpiKind kind, const ConvArgs& c, 
     const ConcEpi e{*(const ConcEpiArgs*)epi};
     return bf16_mode ? conv_direct<bf16>(c, e, st) : conv_direct<float>(c, e, st);
   }
-  if (cfg < 0 || cfg >= kConvDirectCfg) return hipErrorInvalidValue;
+  if (cfg < 0 || (cfg >= kConvDirectCfg && cfg != kConvWideCfg)) return hipErrorInvalidValue;
   if (fused_explicit_pi(kind, epi))
     return bf16_mode ? conv_typed_pi<bf16>(cfg, kind, c, epi, st) : conv_typed_pi<float>(cfg, kind, c, epi, st);
+  if ((kind == EPI_BOUND || kind == EPI_ADJ) && (cfg == kConvWideCfg || epilogue_wide(kind, epi, kRows)))
+    return bf16_mode ? conv_typed_wide<bf16>(cfg, kind, c, epi, st) : conv_typed_wide<float>(cfg, kind, c, epi, st);
   return bf16_mode ? conv_typed<bf16>(cfg, kind, c, epi, st) : conv_typed<float>(cfg, kind, c, epi, st);
 }
 

@@ -3045,6 +3045,15 @@ long instance_work(const gcp_batch_item& it) {
   for (const NodeH& nd : it.net->nodes) width = std::max(width, nd.ld);
   return (long)it.splits->B * it.S * width;
 }
+// Whether a net's rows may be too long for the 32-bit offsets of a grouped
+// launch's tiles (64 rows of four bytes an element within 2 GiB): the net then
+// runs on its own launches, which choose by their sizes.
+bool rows_too_long_to_group(const gcp_net* net) {
+  if (!net) return false;
+  int widest = std::max(net->in_ld, net->n_I);
+  for (const NodeH& nd : net->nodes) widest = std::max(widest, nd.ld);
+  return widest >= 1 << 23;
+}
 // Grouped launches replay a recorded schedule of dense GEMMs with fused
 // epilogues: conv and identity edges and a materialised output Lambda have no
 // recorded form.  Returns what stands in the way, or null.
@@ -3082,7 +3091,7 @@ extern "C" int gcp_optimize_batch(int32_t n_all, const gcp_batch_item* items_all
   std::vector<std::pair<long, int>> big;
   for (int i = 0; i < n_all; ++i) {
     const long w = instance_work(items_all[i]);
-    if (w < alone) grouped.push_back(items_all[i]);
+    if (w < alone && !rows_too_long_to_group(items_all[i].net)) grouped.push_back(items_all[i]);
     else big.push_back({w, i});
   }
   // every item's arguments are checked (and its workspace sized) before

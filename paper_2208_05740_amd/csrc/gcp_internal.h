@@ -106,6 +106,12 @@ inline bool fused_explicit_pi(EpiKind kind, const void* epi) {
   if (kind == EPI_ADJ) return ((const AdjEpiArgs*)epi)->rp.rho != nullptr;
   return false;
 }
+// Whether a tile of that many rows is too large for the 32-bit offsets of the
+// tile epilogues' windows on its arrays (alpha and its moments, a_hat, ..):
+// from 2 GiB on, 8.4 million neurons (or unstable neurons of the net) a row
+// for 64 rows, 134 million for four.
+bool windows_wide(const NodeDev& nd, const RowParams& rp, int rows);
+bool epilogue_wide(EpiKind kind, const void* epi, int rows);
 struct StoreEpiArgs {       // raw accumulate into an fp32 buffer
   int size, ld;
   float scale;
@@ -127,6 +133,8 @@ hipError_t launch_gemm(int bf16, int cfg, EpiKind kind, const GemmArgs& g, const
 int gemm_num_configs();
 void gemm_config_tile(int cfg, int* bm, int* bn);
 bool gemm_config_direct(int cfg);   // K loop without LDS staging (profiler class names)
+// the configuration that launch_gemm runs for a choice: cfg, or a 64-bit tile where cfg's offsets do not reach
+int gemm_config_for(int cfg, EpiKind kind, int bf16, const GemmArgs& g, const void* epi);
 // Several GEMM problems of one instantiation (cfg, kind, sign, precision) in
 // one launch: device tables d_gs[np], d_epis[np] (the kind's *EpiArgs) and
 // d_prefix[np + 1] of cumulative tile counts (total_tiles = d_prefix[np]).
@@ -221,6 +229,9 @@ int conv_num_configs();
 // it applies: concretisation over a source of at most four channels, taps
 // per phase 2x2 at stride 2 or 3x3 at stride 1
 constexpr int kConvDirectCfg = 6;
+// launch_conv's cfg for epilogues with 64-bit addresses, which launches whose
+// arrays need them run whatever their cfg
+constexpr int kConvWideCfg = 7;
 bool conv_direct_ok(const ConvGeom& g, const ConvPlan& plan, EpiKind kind);
 
 // Small independent jobs of a call's start, in one launch.

@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 namespace gcp {
 
 template <typename T, int BM, int BN, int WM, int WN, int BK, bool SIGN, class Epi>
@@ -49,11 +51,14 @@ layer_grouped(const GemmArgs* __restrict__ gs, const Epi* __restrict__ es, const
   layer_tile<T, TM, TN, WM, WN, D, SIGN, Epi>(g, e, t - prefix[lo], sm);
 }
 
-// Tile configurations available to the autotuner: (BM, BN), direct or staged
-// K loop.
+// Tile configurations: (BM, BN).  The autotuner tries the layer tiles, direct
+// or staged K loop; the last three are tiles with 64-bit addresses
+// (gemm_config_for).
 struct TileCfg { int bm, bn; };
-static const TileCfg kCfgs[] = {{64, 64}, {32, 32}, {16, 64}, {64, 64}, {32, 64}, {32, 32}, {16, 64}, {16, 32}};
-static_assert(sizeof(kCfgs) / sizeof(kCfgs[0]) == 8, "tile table");
+static const TileCfg kCfgs[] = {{64, 64}, {32, 32}, {16, 64}, {64, 64}, {32, 64}, {32, 32}, {16, 64}, {16, 32},
+                                {64, 64}, {32, 32}, {16, 32}};
+constexpr int kWide64 = 8, kWide32 = 9, kWide16 = 10;
+static_assert(sizeof(kCfgs) / sizeof(kCfgs[0]) == kWide16 + 1, "tile table");
 int gemm_num_configs() { return (int)(sizeof(kCfgs) / sizeof(kCfgs[0])); }
 void gemm_config_tile(int cfg, int* bm, int* bn) { *bm = kCfgs[cfg].bm; *bn = kCfgs[cfg].bn; }
 bool gemm_config_direct(int cfg) { return cfg == 1 || cfg == 2 || cfg == 7; }
@@ -89,24 +94,48 @@ static hipError_t launch_layer(const GemmLaunch& L, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Bytes of one row of the widest array a tile addresses by 32-bit offsets; 0
-// for epilogues without them.
-template <class Epi, class Args>
-static long row_bytes(const Args& a) {
-  if constexpr (Epi::kPre > 0) return 4l * (a.nd.ld > a.rp.n_I ? a.nd.ld : a.rp.n_I);
-  else return 0;
+bool windows_wide(const NodeDev& nd, const RowParams& rp, int rows) {
+  return 4l * rows * std::max(nd.ld, rp.n_I) >= 1l << 31;
+}
+bool epilogue_wide(EpiKind kind, const void* epi, int rows) {
+  if (kind == EPI_BOUND) return windows_wide(((const BoundEpiArgs*)epi)->nd, ((const BoundEpiArgs*)epi)->rp, rows);
+  if (kind == EPI_ADJ) return windows_wide(((const AdjEpiArgs*)epi)->nd, ((const AdjEpiArgs*)epi)->rp, rows);
+  return false;
+}
+
+// The layer tiles address the operands' rows of a tile by 32-bit offsets from
+// the first one (clamped to the rows there are), and the epilogue's arrays
+// through windows of the tile's rows, whose offsets, rows that do not exist
+// included, stay below kNoElem.  A launch whose rows are too long for its tile
+// runs the 64-bit tile of about that size: in a tile of 64 rows or columns,
+// operand rows beyond 64 MiB (17 million fp32 inputs), epilogue rows from 8.4
+// million neurons (or unstable neurons of the net) on.
+int gemm_config_for(int cfg, EpiKind kind, int bf16_mode, const GemmArgs& g, const void* epi) {
+  if (cfg < 0 || cfg >= kWide64) return cfg;
+  const long bm = kCfgs[cfg].bm, bn = kCfgs[cfg].bn, esz = bf16_mode ? 2 : 4;
+  const long a = std::min<long>(bm, g.M) * g.lda * (g.a_is_sign ? 1 : esz), b = std::min<long>(bn, g.N) * g.ldb * esz;
+  if (a <= 1l << 32 && b <= 1l << 32 && !epilogue_wide(kind, epi, (int)bm) && g.N < 1 << 28) return cfg;
+  return bm * bn >= 32 * 64 ? kWide64 : (bm == 32 ? kWide32 : kWide16);
+}
+
+template <typename T, int BM, int BN, int WM, int WN, bool SIGN, class Epi, class Args>
+static hipError_t launch_cfg(const GemmLaunch& L, hipStream_t st) {
+  constexpr int BK = (sizeof(T) == 4) ? 64 : 128;
+  const GemmArgs& g = *L.g;
+  const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
+  hipLaunchKernelGGL((gemm_epi_kernel<T, BM, BN, WM, WN, BK, SIGN, Epi>), dim3((unsigned)tiles),
+                     dim3(WM * WN * 64), 0, st, g, Epi{*(const Args*)L.epi});
+  return hipGetLastError();
 }
 
 template <typename T, bool SIGN, class Epi, class Args>
 static hipError_t launch_any(int cfg, const GemmLaunch& L, hipStream_t st) {
-  // offsets of a tile's rows stay below 2 GiB (kNoElem): beyond 8 million
-  // neurons a row, 16-row tiles
-  if (!L.d_gs) {
-    const long row = row_bytes<Epi>(*(const Args*)L.epi);
-    if (row * 64 >= 1l << 31) cfg = 7;
-    if (row * 16 >= 1l << 31) return hipErrorInvalidValue;
-  }
+  // (no problem of a group needs 64-bit addresses: its caller leaves such nets out)
+  if (L.d_gs && cfg >= kWide64) cfg = cfg == kWide64 ? 0 : (cfg == kWide32 ? 5 : 7);
   switch (cfg) {
+    case kWide64: return launch_cfg<T, 64, 64, 2, 2, SIGN, Epi, Args>(L, st);
+    case kWide32: return launch_cfg<T, 32, 32, 2, 2, SIGN, Epi, Args>(L, st);
+    case kWide16: return launch_cfg<T, 16, 32, 1, 2, SIGN, Epi, Args>(L, st);
     case 0: case 3: return launch_layer<T, 2, 2, 2, 2, 0, SIGN, Epi, Args>(L, st);
     case 1: return launch_layer<T, 1, 1, 2, 2, kDepth<Epi>, SIGN, Epi, Args>(L, st);
     case 2: return launch_layer<T, 1, 1, 1, 4, kDepth<Epi>, SIGN, Epi, Args>(L, st);
@@ -135,18 +164,8 @@ static hipError_t launch_typed(int cfg, EpiKind kind, int sign, const GemmLaunch
 }
 
 // Explicit-pi epilogues (rho set): instantiated for the small tiles only
-// (their fragments carry rho and its moments); a large-tile choice runs as
-// 32x32.
-template <typename T, int BM, int BN, int WM, int WN, bool SIGN, class Epi, class Args>
-static hipError_t launch_cfg(const GemmLaunch& L, hipStream_t st) {
-  constexpr int BK = (sizeof(T) == 4) ? 64 : 128;
-  const GemmArgs& g = *L.g;
-  const long tiles = (long)((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
-  hipLaunchKernelGGL((gemm_epi_kernel<T, BM, BN, WM, WN, BK, SIGN, Epi>), dim3((unsigned)tiles),
-                     dim3(WM * WN * 64), 0, st, g, Epi{*(const Args*)L.epi});
-  return hipGetLastError();
-}
-
+// (their fragments carry rho and its moments) with 64-bit addresses; a
+// large-tile choice runs as 32x32.
 template <typename T, bool SIGN, class Epi, class Args>
 static hipError_t launch_small(int cfg, const GemmLaunch& L, hipStream_t st) {
   switch (cfg) {
@@ -171,6 +190,7 @@ hipError_t launch_gemm(int bf16_mode, int cfg, EpiKind kind, const GemmArgs& g, 
   GemmLaunch L{&g, epi, nullptr, nullptr, nullptr, 0, 0};
   if (fused_explicit_pi(kind, epi))
     return bf16_mode ? launch_pi<bf16>(cfg, kind, g.a_is_sign, L, st) : launch_pi<float>(cfg, kind, g.a_is_sign, L, st);
+  cfg = gemm_config_for(cfg, kind, bf16_mode, g, epi);
   return bf16_mode ? launch_typed<bf16>(cfg, kind, g.a_is_sign, L, st)
                    : launch_typed<float>(cfg, kind, g.a_is_sign, L, st);
 }
@@ -183,25 +203,27 @@ hipError_t launch_gemm_grouped(int bf16_mode, int cfg, EpiKind kind, int sign, c
 }
 
 // ------------------------------------------------------------------ elementwise
-template <typename T, bool PI>
+template <typename T, bool PI, bool WIDE>
 __global__ void __launch_bounds__(256) bound_elem_kernel(const float* bcast, const void* src, BoundEpiArgs a,
                                                          double* partial, int slot0) {
-  bound_elem_rows<T, PI>(bcast, src, a, partial, slot0, kElemRows * blockIdx.x, blockIdx.y);
+  bound_elem_rows<T, PI, false, WIDE>(bcast, src, a, partial, slot0, kElemRows * blockIdx.x, blockIdx.y);
 }
 
 hipError_t launch_bound_elementwise(int bf16_mode, const float* bcast, const void* src, const BoundEpiArgs& a,
                                     double* partial, int slot0, hipStream_t st) {
   if (a.rp.M <= 0) return hipSuccess;
   dim3 grid((a.rp.M + kElemRows - 1) / kElemRows, (a.nd.size + 255) / 256);
-  const bool pi = a.rp.rho != nullptr;
-  if (bf16_mode && pi)
-    hipLaunchKernelGGL((bound_elem_kernel<bf16, true>), grid, dim3(256), 0, st, bcast, src, a, partial, slot0);
-  else if (bf16_mode)
-    hipLaunchKernelGGL((bound_elem_kernel<bf16, false>), grid, dim3(256), 0, st, bcast, src, a, partial, slot0);
-  else if (pi)
-    hipLaunchKernelGGL((bound_elem_kernel<float, true>), grid, dim3(256), 0, st, bcast, src, a, partial, slot0);
-  else
-    hipLaunchKernelGGL((bound_elem_kernel<float, false>), grid, dim3(256), 0, st, bcast, src, a, partial, slot0);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, bcast, src, a, partial, slot0); };
+  if (a.rp.rho != nullptr) {      // (its explicit-pi form has 64-bit addresses)
+    if (bf16_mode) go(bound_elem_kernel<bf16, true, true>);
+    else go(bound_elem_kernel<float, true, true>);
+  } else if (windows_wide(a.nd, a.rp, kElemRows)) {
+    if (bf16_mode) go(bound_elem_kernel<bf16, false, true>);
+    else go(bound_elem_kernel<float, false, true>);
+  } else {
+    if (bf16_mode) go(bound_elem_kernel<bf16, false, false>);
+    else go(bound_elem_kernel<float, false, false>);
+  }
   return hipGetLastError();
 }
 

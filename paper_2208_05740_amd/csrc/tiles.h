@@ -251,6 +251,8 @@ __device__ inline void gemm_tile(const GemmArgs& g, const Epi& epi, int vt) {
 // with the next tile's loads ahead of the epilogue measured slower (three
 // waves per SIMD, 43 us for the relaxation).  Both forms accumulate the
 // fragments in the order of gemm_tile_lds, so the results are the same bits.
+// Operand rows and epilogue windows have 32-bit offsets: launches that these do
+// not reach run gemm_tile_lds (gemm_config_for).
 template <typename T, int TM, int TN, int WM, int WN, int D>
 struct LayerLds {
   static constexpr int BM = WM * TM * 16, BN = WN * TN * 16, BK = 128 / (int)sizeof(T), LD = BK + Op<T>::VEC;
@@ -324,10 +326,10 @@ struct StagedLoop {
     Bb = (const char*)g.Bt + (size_t)n0 * g.ldb * sizeof(T);
 #pragma unroll
     for (int it = 0; it < AIT; ++it)
-      oa[it] = (uint32_t)min(min(tid / CV + it * (NT / CV), BM - 1), g.M - 1 - m0) * (uint32_t)(g.lda * AB);
+      oa[it] = (uint32_t)min(min(tid / CV + it * (NT / CV), BM - 1), g.M - 1 - m0) * ((uint32_t)g.lda * AB);
 #pragma unroll
     for (int it = 0; it < BIT; ++it)
-      ob[it] = (uint32_t)min(min(tid / CV + it * (NT / CV), BN - 1), g.N - 1 - n0) * (uint32_t)(g.ldb * (int)sizeof(T));
+      ob[it] = (uint32_t)min(min(tid / CV + it * (NT / CV), BN - 1), g.N - 1 - n0) * ((uint32_t)g.ldb * (uint32_t)sizeof(T));
     fetch(g, 0, 0);
     fetch(g, min(1, last), 1);
   }
@@ -511,9 +513,9 @@ __device__ __forceinline__ void layer_tile(const GemmArgs& g, const Epi& epi, in
     const int nfull = g.K / KC, last = max(nfull - 1, 0);
     uint32_t oa[TM], ob[TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) oa[i] = (uint32_t)((min((wm * TM + i) * 16 + li, g.M - 1 - m0)) * g.lda) * AB;
+    for (int i = 0; i < TM; ++i) oa[i] = (uint32_t)min((wm * TM + i) * 16 + li, g.M - 1 - m0) * (uint32_t)g.lda * AB;
 #pragma unroll
-    for (int k = 0; k < TN; ++k) ob[k] = (uint32_t)((min((wn * TN + k) * 16 + li, g.N - 1 - n0)) * g.ldb) * (uint32_t)sizeof(T);
+    for (int k = 0; k < TN; ++k) ob[k] = (uint32_t)min((wn * TN + k) * 16 + li, g.N - 1 - n0) * (uint32_t)g.ldb * (uint32_t)sizeof(T);
     AV fa[D][TM];
     uint4 fb[D][TN];
     // K step s (lane offset ko elements) into slot d
@@ -600,8 +602,8 @@ __device__ __forceinline__ void layer_tile(const GemmArgs& g, const Epi& epi, in
 // rows, so a neuron's data is read once for them and their loads are in
 // flight together; one row partial per (row, column block), summed over the
 // block in a fixed order.  PI selects the explicit-pi relaxation (a.rp.rho
-// set).
-template <typename T, bool PI, bool OPAQUE = false>
+// set); WIDE: arrays too large for the windows (windows_wide).
+template <typename T, bool PI, bool OPAQUE = false, bool WIDE = false>
 __device__ __forceinline__ void bound_elem_rows(const float* bcast, const void* src, const BoundEpiArgs& a, double* partial,
                                        int slot0, int r0, int cb) {
   constexpr int R = kElemRows;
@@ -614,7 +616,7 @@ __device__ __forceinline__ void bound_elem_rows(const float* bcast, const void* 
   double rs[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) rs[q] = 0.0;
-  if constexpr (!PI && !OPAQUE) {
+  if constexpr (!PI && !OPAQUE && !WIDE) {
     // as a layer tile of one column per lane (r0 is wave-uniform): bound by the
     // wave's instructions and its alpha and cut loads; with 64-bit addresses
     // and a division per row, 784-256x6 MLP: 9 rows 4.3 -> 3.4 us, 9216 rows

@@ -116,3 +116,61 @@ def test_bf16_convs_that_one_row_slabs_took_are_taken(tmp_path):
 def test_fp32_convs_that_one_row_slabs_took_are_taken(tmp_path):
     lost, cases = _conv_sweep(tmp_path)
     assert lost[0] == 0, (lost, cases[:10])
+
+
+# Every offset that a layer tile forms in 32 bits, in 64: operand rows of the
+# tile (those that exist) up to their last vector, and the windows of the
+# epilogue, rows that do not exist included, below 2^31.
+ADDRESSES = r"""
+#include "gcp_internal.h"
+#include <algorithm>
+#include <cstdio>
+using namespace gcp;
+int main() {
+  const long widths[] = {16, 784, 1 << 20, (1 << 23) - 16, 1 << 23, 1 << 24, 17039360, 17039376, (1 << 25) - 16, 1 << 25,
+                         34078736, 1 << 26, (1 << 27) - 16, 1 << 27, 200000000};
+  const EpiKind kinds[] = {EPI_STORE, EPI_BOUND, EPI_CONC, EPI_ADJ, EPI_AHAT};
+  long n = 0, wide = 0, bad = 0, moved = 0;
+  for (long kw : widths) for (long nw : widths) for (long ni : widths) for (EpiKind kind : kinds)
+    for (int bf16 = 0; bf16 < 2; ++bf16) for (int sign = 0; sign < (kind == EPI_ADJ || kind == EPI_STORE ? 2 : 1); ++sign)
+      for (int M : {1, 9, 37, 64, 36864}) for (int cfg = 0; cfg < 8; ++cfg) {
+        GemmArgs g{};
+        g.M = M; g.N = (int)nw; g.K = (int)kw; g.lda = (int)kw; g.ldb = (int)kw; g.a_is_sign = sign;
+        BoundEpiArgs be{}; AdjEpiArgs ae{}; ConcEpiArgs ce{}; StoreEpiArgs se{};
+        be.nd.ld = ae.nd.ld = (int)nw;
+        be.rp.n_I = ae.rp.n_I = ce.rp.n_I = (int)ni;
+        const void* epi = kind == EPI_ADJ ? (void*)&ae : kind == EPI_CONC ? (void*)&ce : kind == EPI_STORE ? (void*)&se : (void*)&be;
+        const int run = gemm_config_for(cfg, kind, bf16, g, epi);
+        ++n;
+        int bm, bn;
+        gemm_config_tile(run, &bm, &bn);
+        if (run >= 8) {
+          ++wide;
+          if (std::max({kw, nw, kind == EPI_BOUND || kind == EPI_ADJ ? ni : 0}) < 1 << 23) ++moved;
+          continue;
+        }
+        const long esz = bf16 ? 2 : 4, ab = sign ? 1 : esz;
+        const long a = ((std::min(bm, M) - 1) * kw + kw) * ab - 1, b = ((std::min<long>(bn, nw) - 1) * kw + kw) * esz - 1;
+        bool ok = run == cfg && a <= 0xffffffffl && b <= 0xffffffffl && nw * 16 - 1 <= 0xffffffffl;
+        if (kind == EPI_BOUND || kind == EPI_ADJ)
+          for (long p : {nw, ni}) ok = ok && bm * p * 4 < 0x80000000l && 0x80000000l + 3 * p * 4 <= 0xffffffffl;
+        if (!ok && bad++ < 10) printf("cfg %d -> %d kind %d bf16 %d sign %d M %d N %ld K %ld n_I %ld\n", cfg, run, kind, bf16, sign, M, nw, kw, ni);
+      }
+  // four rows: the elementwise relaxation and the conv lists
+  for (long p : widths)
+    for (int swap = 0; swap < 2; ++swap) {
+      NodeDev nd{}; RowParams rp{};
+      nd.ld = (int)(swap ? 16 : p); rp.n_I = (int)(swap ? p : 16);
+      const bool fits = 16 * p < 0x80000000l;
+      if (windows_wide(nd, rp, 4) == fits) ++bad;
+    }
+  printf("%ld %ld %ld %ld\n", n, wide, bad, moved);
+}
+"""
+
+
+def test_tiles_reach_their_rows_or_give_way_to_64_bit_tiles(tmp_path):
+    *cases, last = _run(tmp_path, ADDRESSES)
+    n, wide, bad, moved = [int(x) for x in last.split()]
+    assert n > 100000 and wide > 1000 and bad == 0, (last, cases)
+    assert moved == 0, last      # rows of up to 8 million keep the tile that was chosen
