@@ -2409,12 +2409,18 @@ void bound_impl(const gcp_net* net_c, const double* x0, double eps, const double
   AdjPass ap{c, bf16, AdamArgs{0, 0.f, 0.f, 0.f, nullptr}, d_alpha, d_beta, nullptr, nullptr,
              nullptr, nullptr, nullptr, nullptr, rho ? d_rho : nullptr};
   const size_t n_beta = (size_t)c.M * splits->K;
-  const bool beta_late = d_beta && beta && d_beta < beta + n_beta && beta < d_beta + n_beta;
+  // (an output in the memory of an input that the bound pass reads last, beta,
+  // gamma or C, is cleared after it)
+  auto clears = [&](const void* in, size_t bytes) {
+    const char *p = (const char*)in, *q = (const char*)d_beta;
+    return p && q && q < p + bytes && p < q + n_beta * 4;
+  };
+  const bool beta_late = clears(beta, n_beta * 4) || clears(gamma, (size_t)c.M * c.N * 4) ||
+                         clears(C, (size_t)c.S * net->nodes[net->out].size * 8);
   Prologue pr(c.st);
   if (c.N > 0) pr.transpose(gamma, c.M, c.N, c.ws->gammaT.as<float>(), c.rp.mp);
   if (!net->out_general) pr.constants(c);
   if (grads) {
-    // (an output in beta's own memory is cleared after the bound pass has read it)
     if (!beta_late) pr.zero(d_beta, c.M, splits->K);
     ap.prepare(pr);
   }
