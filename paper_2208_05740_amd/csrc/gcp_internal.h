@@ -247,9 +247,11 @@ struct PrepJob {
 constexpr int kPrepMax = 16;
 struct PrepArgs {
   int n;
+  int blocks;              // workgroups of all jobs
   int first[kPrepMax];     // first workgroup of each job
   PrepJob job[kPrepMax];
 };
+dim3 prep_grid(int blocks);
 hipError_t launch_prep(const PrepJob* jobs, int n, hipStream_t st);
 // rows g0 .. g0 + rows - 1 of {e_0 .. e_(d-1), -e_0 .. -e_(d-1)}, [rows][d]
 hipError_t launch_unit_rows(double* C, int rows, int d, int g0, hipStream_t st);

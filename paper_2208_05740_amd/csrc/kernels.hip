@@ -417,10 +417,12 @@ __device__ inline void wx0_rows(const ConvGeom& cg, int kind, const float* W, in
 
 __global__ void __launch_bounds__(256) prep_kernel(PrepArgs a) {
   __shared__ float t[32][33];
+  const int blk = blockIdx.y * gridDim.x + blockIdx.x;
+  if (blk >= a.blocks) return;
   int i = 0;
-  while (i + 1 < a.n && (int)blockIdx.x >= a.first[i + 1]) ++i;
+  while (i + 1 < a.n && blk >= a.first[i + 1]) ++i;
   const PrepJob& p = a.job[i];
-  const int b = blockIdx.x - a.first[i];
+  const int b = blk - a.first[i];
   switch (p.kind) {
     case PREP_CONST: out_const_rows((const double*)p.a, p.n0, p.n1, (const float*)p.b, (double*)p.out, b); break;
     case PREP_CHAT: {
@@ -456,6 +458,13 @@ static long prep_blocks(const PrepJob& p) {
   return 0;
 }
 
+// (in rows of 65536 workgroups: a grid's x has less than 2^32 threads, which
+// the columns of c-hat pass at 4096 spec rows over a million neurons)
+dim3 prep_grid(int blocks) {
+  const int x = std::min(blocks, 1 << 16);
+  return dim3(x, (blocks + x - 1) / x);
+}
+
 hipError_t launch_prep(const PrepJob* jobs, int n, hipStream_t st) {
   if (n > kPrepMax) return hipErrorInvalidValue;
   PrepArgs a{};
@@ -466,10 +475,11 @@ hipError_t launch_prep(const PrepJob* jobs, int n, hipStream_t st) {
     a.first[a.n] = (int)at;
     a.job[a.n++] = jobs[i];
     at += nb;
-    if (at > 0x7fffffffL) return hipErrorInvalidValue;
+    if (at > 0x7fff0000L) return hipErrorInvalidValue;     // (whole rows of workgroups count in an int)
   }
   if (at == 0) return hipSuccess;
-  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)at), dim3(256), 0, st, a);
+  a.blocks = (int)at;
+  hipLaunchKernelGGL(prep_kernel, prep_grid(a.blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

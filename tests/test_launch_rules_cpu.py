@@ -174,3 +174,22 @@ def test_tiles_reach_their_rows_or_give_way_to_64_bit_tiles(tmp_path):
     n, wide, bad, moved = [int(x) for x in last.split()]
     assert n > 100000 and wide > 1000 and bad == 0, (last, cases)
     assert moved == 0, last      # rows of up to 8 million keep the tile that was chosen
+
+
+GRID = r"""
+#include "gcp_internal.h"
+#include <cstdio>
+int main() {
+  for (int n : {1, 2, 65535, 65536, 65537, 1 << 24, (1 << 24) + 1, 100000007, 0x7fff0000}) {
+    const dim3 g = gcp::prep_grid(n);
+    const unsigned long all = (unsigned long)g.x * g.y;
+    printf("%d %d\n", n, g.x * 256ul < 1ul << 32 && g.y <= 65535 && g.z == 1 && all >= (unsigned long)n && all < (unsigned long)n + g.x &&
+                              all <= 0x7fffffff);
+  }
+}
+"""
+
+
+def test_start_of_call_grid_is_launchable_and_covers_its_jobs(tmp_path):
+    out = [line.split() for line in _run(tmp_path, GRID)]
+    assert len(out) == 9 and all(ok == "1" for _, ok in out), out
