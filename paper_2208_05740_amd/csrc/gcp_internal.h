@@ -295,6 +295,7 @@ struct SlackArgs {
   const float* gammaT; int N; const double* kap; double c_cut, c_d;  // kap [3][N]: kappa, kappa_in, |d|
   double* out;                       // partial slot [mp]: minus the slack of each row
 };
+int slack_grid(int M);   // workgroups of its row kernel
 hipError_t launch_slack(const SlackArgs& a, hipStream_t st);
 
 // d bound/d gamma from the entry pieces; Adam on gammaT (moments m, v are

@@ -675,6 +675,8 @@ __global__ void __launch_bounds__(256) slack_rows_kernel(SlackArgs a) {
   }
 }
 
+int slack_grid(int M) { return (M + 4 * kSlackRows - 1) / (4 * kSlackRows); }
+
 hipError_t launch_slack(const SlackArgs& a, hipStream_t st) {
   if (a.M <= 0) return hipSuccess;
   if (a.n_nodes <= 0 || a.n_nodes > kSlackMaxNodes) return hipErrorInvalidValue;
@@ -683,7 +685,7 @@ hipError_t launch_slack(const SlackArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(slack_weights_kernel, dim3((ldmax + 255) / 256, a.n_nodes), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(slack_rows_kernel, dim3((a.M + 3) / 4), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(slack_rows_kernel, dim3(slack_grid(a.M)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

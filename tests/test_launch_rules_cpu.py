@@ -193,3 +193,14 @@ int main() {
 def test_start_of_call_grid_is_launchable_and_covers_its_jobs(tmp_path):
     out = [line.split() for line in _run(tmp_path, GRID)]
     assert len(out) == 9 and all(ok == "1" for _, ok in out), out
+
+
+def test_slack_grid_has_no_idle_workgroup(tmp_path):
+    # 16 rows a workgroup
+    out = _run(tmp_path, '''
+#include "gcp_internal.h"
+#include <cstdio>
+int main() { for (int M : {1, 15, 16, 17, 333, 36864}) printf("%d %d\\n", M, gcp::slack_grid(M)); }
+''')
+    for M, g in (map(int, line.split()) for line in out):
+        assert 16 * (g - 1) < M <= 16 * g, (M, g)
