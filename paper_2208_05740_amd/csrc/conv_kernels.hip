@@ -255,24 +255,34 @@ static ConvPlan conv_plan_row(const ConvGeom& g, int trans) {
 // (four bytes per K index), may still not fit: 320 -> 64 channels of 3x3 at
 // 8x8 are 150 KB of slab and 11.8 KB of tables in fp32, which takes another
 // plan, and half that slab in bf16, which keeps this one.
-ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16) {
+ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16, bool* by_type) {
   ConvPlan P = plan_dims(g, trans);
   P.rb = 4;
-  if (trans && P.Nch <= 4 && direct_shape(P))   // bands of the direct kernel: one 64-position chunk per wave
-    for (int bh = P.He; bh >= 1; --bh) {
-      plan_bands(P, trans, bh);
-      if (direct_chunks(P) <= kDirNW && plan_items(P) <= kItems &&
-          16 * std::max(slab_cells(P), out_cells(P)) <= kSlabBudget[1] && conv_fits(P, bf16))
-        return P;
-    }
-  for (long budget : kSlabBudget)
-    for (int bh = P.He; bh >= 1; --bh) {
-      plan_bands(P, trans, bh);
-      if (plan_items(P) <= kItems && 16 * std::max(slab_cells(P), out_cells(P)) <= budget && conv_fits(P, bf16)) return P;
-    }
-  plan_bands(P, trans, 1);   // more channels or positions than the waves hold: results beside the slab
-  if (16 * (slab_cells(P) + out_cells(P)) <= kSlabBudget[1] && conv_fits(P, bf16)) return P;
-  return conv_plan_row(g, trans);
+  bool tight = false;
+  auto fits = [&] {
+    const bool ok = conv_fits(P, bf16);
+    tight = tight || !ok;
+    return ok;
+  };
+  auto pick = [&] {
+    if (trans && P.Nch <= 4 && direct_shape(P))   // bands of the direct kernel: one 64-position chunk per wave
+      for (int bh = P.He; bh >= 1; --bh) {
+        plan_bands(P, trans, bh);
+        if (direct_chunks(P) <= kDirNW && plan_items(P) <= kItems &&
+            16 * std::max(slab_cells(P), out_cells(P)) <= kSlabBudget[1] && fits())
+          return true;
+      }
+    for (long budget : kSlabBudget)
+      for (int bh = P.He; bh >= 1; --bh) {
+        plan_bands(P, trans, bh);
+        if (plan_items(P) <= kItems && 16 * std::max(slab_cells(P), out_cells(P)) <= budget && fits()) return true;
+      }
+    plan_bands(P, trans, 1);   // more channels or positions than the waves hold: results beside the slab
+    return 16 * (slab_cells(P) + out_cells(P)) <= kSlabBudget[1] && fits();
+  };
+  if (!pick()) P = conv_plan_row(g, trans);
+  if (by_type) *by_type = tight;
+  return P;
 }
 
 long conv_row_slab(const ConvGeom& g, int trans) {

@@ -477,6 +477,28 @@ void upload_band_list(const ConvPlan& P, const std::vector<int32_t>& pick, const
   off.upload(o);
 }
 
+// The plans of a conv edge with their tables and lists; src and dst null where
+// they have no relaxation.
+void make_sides(EdgeH& E, const NodeH* src, const NodeH* dst) {
+  for (int t = 0; t < 2; ++t) {
+    bool by_type;
+    E.side[t][0].plan = conv_plan(E.cg, t, 0, &by_type);
+    if (by_type) {
+      E.side[t][1].plan = conv_plan(E.cg, t, 1);
+      E.n_side[t] = 2;
+    }
+    const NodeH* n = t ? src : dst;
+    std::vector<int32_t> unstable;
+    for (int j = 0; n && j < n->size; ++j)
+      if (n->rank_h[j] >= 0) unstable.push_back(j);
+    for (int b = 0; b < E.n_side[t]; ++b) {
+      ConvSide& sd = E.side[t][b];
+      sd.tab.upload(conv_tables(sd.plan, t));
+      if (n) upload_band_list(sd.plan, unstable, &n->kind_h, sd.uns, sd.uns_off);
+    }
+  }
+}
+
 int node_size_of(const gcp_net* net, int src) { return src < 0 ? net->in_size : net->nodes[src].size; }
 int node_ld_of(const gcp_net* net, int src) { return src < 0 ? net->in_ld : net->nodes[src].ld; }
 
@@ -652,14 +674,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
         conv_pack_weights(E->cg, 1, raw.data(), ft.data());
         if (conv_row_slab(E->cg, 0) > 48 * 1024 || conv_row_slab(E->cg, 1) > 48 * 1024)
           fail(GCP_EUNSUPPORTED, "conv rows too wide for an LDS slab");
-        for (int t = 0; t < 2; ++t) {
-          const ConvPlan p32 = conv_plan(E->cg, t, 0), p16 = conv_plan(E->cg, t, 1);
-          E->n_side[t] = p32.BH == p16.BH && p32.rb == p16.rb ? 1 : 2;
-          for (int b = 0; b < E->n_side[t]; ++b) {
-            E->side[t][b].plan = b ? p16 : p32;
-            E->side[t][b].tab.upload(conv_tables(E->side[t][b].plan, t));
-          }
-        }
+        make_sides(*E, ed.src >= 0 ? &net->nodes[ed.src] : nullptr, n.relu ? &n : nullptr);
         E->ldk_f = kf;
         E->ldk_t = kt;
         E->W32.upload(fw); E->W16.upload(to_bf16(fw));
@@ -683,19 +698,6 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
             }
         e_wy.push_back(std::move(wy));
         e_terms.push_back((double)n.c * ed.kh * ed.kw);
-        auto unstable_of = [](const NodeH& t) {
-          std::vector<int32_t> u;
-          for (int j = 0; j < t.size; ++j)
-            if (t.rank_h[j] >= 0) u.push_back(j);
-          return u;
-        };
-        for (int t = 0; t < 2; ++t) {
-          const NodeH* ln = t ? (ed.src >= 0 ? &net->nodes[ed.src] : nullptr) : (n.relu ? &n : nullptr);
-          for (int b = 0; ln && b < E->n_side[t]; ++b) {
-            ConvSide& sd = E->side[t][b];
-            upload_band_list(sd.plan, unstable_of(*ln), &ln->kind_h, sd.uns, sd.uns_off);
-          }
-        }
       } else if (ed.kind == GCP_EDGE_IDENTITY) {
         if (E->d_src != E->d_dst) fail(GCP_EINVAL, "identity edge between different sizes");
         if (ed.src < 0) e_wy.emplace_back(E->d_dst, 1.0);

@@ -215,7 +215,9 @@ struct ConvPlan {
 // Bytes of the slab that holds one batch row in fp32, in bands as high as it
 // allows: a net is created if it has at most 48 KB, in both directions.
 long conv_row_slab(const ConvGeom& g, int trans);
-ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16);
+// (by_type, optional: whether bf16 can have another plan than fp32, as asked
+// for fp32)
+ConvPlan conv_plan(const ConvGeom& g, int trans, int bf16, bool* by_type = nullptr);
 // whether launch_conv takes the plan, in every shape of workgroup
 bool conv_fits(const ConvPlan& P, int bf16);
 std::vector<int32_t> conv_tables(const ConvPlan& P, int trans);

@@ -86,6 +86,11 @@ int main() {
         made = made && r[t].slab <= 48 * 1024;
       }
       if (!made) continue;
+      for (int t = 0; t < 2; ++t) {
+        bool by_type;      // else bf16 runs fp32's plan
+        const ConvPlan a = conv_plan(g, t, 0, &by_type), b = conv_plan(g, t, 1);
+        if (!by_type && (a.BH != b.BH || a.rb != b.rb)) return 2;
+      }
       for (int t = 0; t < 2; ++t)
         for (int bf16 = 0; bf16 < 2; ++bf16) {
           if (r[t].lds[bf16] > 64 * 1024) continue;
