@@ -763,9 +763,19 @@ int heuristic_cfg(int M, int N) {
 // Process-wide tile cache.  With GCP_TILE_CACHE=<file> decisions are read
 // from the file at first use (and again whenever the variable names another
 // file) and every new decision is appended, so a later process (for example
-// a profiler run) launches exactly the same tiles.
+// a profiler run) launches exactly the same tiles.  The entry of an empty
+// product, kTableKey, gives the table of tiles that the lines after it number;
+// lines before any such entry are of table 1, whose dense numbers 1, 2 and 3
+// were 128x64, 64x128 and 128x128 and whose 7 was staged.  Those choices are
+// made again (the same numbers are direct tiles now, at 9216 rows 15.0 ms
+// against 10.1 for an ascent of the 784-256x6 MLP); where no trial may make
+// them (GCP_AUTOTUNE=0) the numbers stand as they are written.
+constexpr int kPiKey = 16;   // explicit-pi launches: tile-cache keys of their own (epilogue kind + kPiKey)
 struct TileCache {
+  static constexpr int kTable = 2;
+  static constexpr const char* kTableKey = "gemm.k0.b0.s0.M0.N0.K0";
   std::mutex mu;
+  int file_table = 1;         // table of the file's last lines
   bool loaded = false;
   std::string loaded_path;    // the file the decisions came from ("" = none)
   std::map<std::string, int> m;
@@ -777,15 +787,22 @@ struct TileCache {
     if (loaded && ps == loaded_path) return;
     loaded = true;
     loaded_path = ps;
+    file_table = 1;
     m.clear();
     if (!p) return;
     FILE* f = std::fopen(p, "r");
     if (!f) return;
     char key[160];
     int cfg;
-    while (std::fscanf(f, "%159s %d", key, &cfg) == 2)
-      if (cfg >= 0 && cfg < 16) m[key] = cfg;
+    while (std::fscanf(f, "%159s %d", key, &cfg) == 2) {
+      if (std::strcmp(key, kTableKey) == 0) file_table = cfg;
+      else if (cfg >= 0 && cfg < 16 && !(file_table < kTable && renumbered(key, cfg) && autotune_enabled())) m[key] = cfg;
+    }
     std::fclose(f);
+  }
+  static bool renumbered(const char* key, int cfg) {
+    int kind;
+    return std::sscanf(key, "gemm.k%d.", &kind) == 1 && kind < kPiKey && (cfg == 1 || cfg == 2 || cfg == 3 || cfg == 7);
   }
   void store(const std::string& key, int cfg) {
     m[key] = cfg;
@@ -793,6 +810,7 @@ struct TileCache {
     if (!p) return;
     FILE* f = std::fopen(p, "a");
     if (!f) return;
+    if (file_table != kTable) std::fprintf(f, "%s %d\n", kTableKey, file_table = kTable);
     std::fprintf(f, "%s %d\n", key.c_str(), cfg);
     std::fclose(f);
   }
@@ -828,9 +846,7 @@ Cands conc_conv_cands(const ConvGeom& g, const ConvPlan& plan) {
   if (conv_direct_enabled() && conv_direct_ok(g, plan, EPI_CONC)) return Cands{{kConvDirectCfg}, kConvDirectCfg};
   return conv_cands();
 }
-// Explicit-pi launches: the shapes their epilogues are instantiated for, and
-// tile-cache keys of their own (epilogue kind + kPiKey).
-constexpr int kPiKey = 16;
+// Explicit-pi launches: the shapes their epilogues are instantiated for.
 Cands pi_dense_cands(int M, int N) { return Cands{{5, 6, 7}, pi_cfg(heuristic_cfg(M, N))}; }
 Cands pi_conv_cands() { return Cands{{0, 2}, 2}; }
 
