@@ -477,6 +477,27 @@ void upload_band_list(const ConvPlan& P, const std::vector<int32_t>& pick, const
   off.upload(o);
 }
 
+// sum |W| y of every output of a conv, y of its source (null: 1)
+std::vector<double> conv_abs_sums(const ConvGeom& g, const float* raw, const double* src) {
+  std::vector<double> out((size_t)g.co * g.ho * g.wo);
+  size_t j = 0;
+  for (int o = 0; o < g.co; ++o)
+    for (int y = 0; y < g.ho; ++y)
+      for (int x = 0; x < g.wo; ++x, ++j) {
+        double t = 0.0;
+        for (int c = 0; c < g.ci; ++c)
+          for (int ky = 0; ky < g.kh; ++ky)
+            for (int kx = 0; kx < g.kw; ++kx) {
+              const int iy = y * g.stride - g.pad + ky, ix = x * g.stride - g.pad + kx;
+              if (iy < 0 || iy >= g.hi || ix < 0 || ix >= g.wi) continue;
+              t += std::fabs((double)raw[(((size_t)o * g.ci + c) * g.kh + ky) * g.kw + kx]) *
+                   (src ? src[((size_t)c * g.hi + iy) * g.wi + ix] : 1.0);
+            }
+        out[j] = t;
+      }
+  return out;
+}
+
 // The plans of a conv edge with their tables and lists; src and dst null where
 // they have no relaxation.
 void make_sides(EdgeH& E, const NodeH* src, const NodeH* dst) {
@@ -680,23 +701,7 @@ void build_net(const gcp_net_desc* d, gcp_net* net) {
         E->W32.upload(fw); E->W16.upload(to_bf16(fw));
         E->WT32.upload(ft); E->WT16.upload(to_bf16(ft));
         E->WT16f.upload(bf16_as_f32(to_bf16(ft)));
-        std::vector<double> wy(E->d_dst, 0.0);
-        for (int o = 0; o < n.c; ++o)
-          for (int y = 0; y < ho; ++y)
-            for (int x = 0; x < wo; ++x) {
-              double t = 0.0;
-              for (int cc = 0; cc < ci; ++cc)
-                for (int ky = 0; ky < ed.kh; ++ky)
-                  for (int kx = 0; kx < ed.kw; ++kx) {
-                    const int iy = y * ed.stride - ed.pad + ky, ix = x * ed.stride - ed.pad + kx;
-                    if (iy < 0 || iy >= hi || ix < 0 || ix >= wi) continue;
-                    const size_t src_j = ((size_t)cc * hi + iy) * wi + ix;
-                    t += std::fabs((double)raw[(((size_t)o * ci + cc) * ed.kh + ky) * ed.kw + kx]) *
-                         (ed.src < 0 ? 1.0 : net->nodes[ed.src].y_h[src_j]);
-                  }
-              wy[((size_t)o * ho + y) * wo + x] = t;
-            }
-        e_wy.push_back(std::move(wy));
+        e_wy.push_back(conv_abs_sums(E->cg, raw.data(), ed.src < 0 ? nullptr : net->nodes[ed.src].y_h.data()));
         e_terms.push_back((double)n.c * ed.kh * ed.kw);
       } else if (ed.kind == GCP_EDGE_IDENTITY) {
         if (E->d_src != E->d_dst) fail(GCP_EINVAL, "identity edge between different sizes");
