@@ -5,6 +5,7 @@
 // the caller's stream; no host synchronisation inside gcp_bound/gcp_optimize
 // unless GCP_FLAG_VALIDATE is set.
 #include "../../include/gcp.h"
+#include "call_arena.h"
 #include "gcp_internal.h"
 
 #include <hip/hip_runtime.h>
@@ -139,65 +140,37 @@ std::string cls_name(const char* kind, int bf16, int sign, int cfg) {
 // launcher instantiates those epilogues for the small tiles only).
 int pi_cfg(int cfg) { return (cfg == 6 || cfg == 7) ? cfg : 5; }
 
-// Device memory of one call that makes and drops whole networks: buffers are
-// cut from chunks that are kept until the call ends, zero-filled when they are
-// made and again by rewind(), which the caller runs once nothing of the
-// previous network is left, on the device or the host.  The intermediate
-// bounds of the CNN (three prefix networks) spent 5.7 of 9.7 ms in 133
-// allocations and frees; with the arena they take 5.9 ms.
-class CallArena {
-  struct Chunk { char* p; size_t bytes, used; };
-  std::vector<Chunk> chunks;
-  static constexpr size_t kChunk = (size_t)32 << 20, kAlign = 256;
+struct HipMem {
+  static char* try_alloc(size_t n) {
+    char* p = nullptr;
+    if (hipMalloc((void**)&p, n) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  static char* alloc(size_t n) {
+    char* p = try_alloc(n);
+    if (!p) hip_check(hipErrorOutOfMemory, "hipMalloc");
+    return p;
+  }
+  static void free(char* p) { (void)hipFree(p); }
+  static void wait() { (void)hipDeviceSynchronize(); }
   static void clear(void* p, size_t n) {
     hip_check(hipMemset(p, 0, n), "hipMemset");
     hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
   }
- public:
-  CallArena() = default;
-  CallArena(const CallArena&) = delete;
-  CallArena& operator=(const CallArena&) = delete;
-  ~CallArena() {
-    (void)hipDeviceSynchronize();     // an error may have left work in flight
-    for (Chunk& c : chunks) (void)hipFree(c.p);
-  }
-  void* take(size_t n) {
-    n = (n + kAlign - 1) / kAlign * kAlign;
-    for (Chunk& c : chunks)
-      if (c.bytes - c.used >= n) {
-        void* q = c.p + c.used;
-        c.used += n;
-        return q;
-      }
-    Chunk c{nullptr, std::max(n, kChunk), n};
-    if (hipMalloc((void**)&c.p, c.bytes) != hipSuccess) {   // give back what this network does not use, ask for n alone
-      (void)hipGetLastError();
-      for (size_t i = chunks.size(); i-- > 0;)
-        if (chunks[i].used == 0) {
-          (void)hipFree(chunks[i].p);
-          chunks.erase(chunks.begin() + i);
-        }
-      c.bytes = n;
-      hip_check(hipMalloc((void**)&c.p, c.bytes), "hipMalloc");
-    }
-    chunks.push_back(c);
-    clear(c.p, c.bytes);
-    return c.p;
-  }
-  void rewind() {
-    for (Chunk& c : chunks) {
-      if (c.used) clear(c.p, c.used);
-      c.used = 0;
-    }
-  }
 };
 // The arena of the call this thread is in, if any (ArenaScope).
-thread_local CallArena* t_arena = nullptr;
+thread_local CallArena<HipMem>* t_arena = nullptr;
 struct ArenaScope {
-  CallArena arena;
-  CallArena* outer = t_arena;
+  CallArena<HipMem> arena;
+  CallArena<HipMem>* outer = t_arena;
   ArenaScope() { t_arena = &arena; }
   ~ArenaScope() { t_arena = outer; }
+  bool on() const { return t_arena == &arena; }
+  void off() {
+    arena.give_back();
+    t_arena = outer;
+  }
 };
 
 // Owned device allocation (zero-filled at allocation), or a borrowed view of
@@ -3414,76 +3387,86 @@ extern "C" int gcp_crown_bounds_domain(const gcp_net_desc* desc, const double* x
     const int d = nk.c * nk.h * nk.w;
     if (d <= 0) fail(GCP_EINVAL, "bad node shape");
     if (!lower[k] || !upper[k]) fail(GCP_EINVAL, "null bound output of node " + std::to_string(k));
-    if (k > 0) scope.arena.rewind();    // (the last bounds of node k - 1 were waited for)
-    // the prefix network: nodes 0..k with node k as its output (the
-    // pre-activation), earlier nodes carrying the bounds found so far
-    gcp_net_desc sub{desc->in_c, desc->in_h, desc->in_w, k + 1, nodes.data()};
-    for (int i = 0; i < k; ++i) {
-      nodes[i].lower = L[i].data();
-      nodes[i].upper = U[i].data();
-    }
-    nodes[k] = nk;
-    nodes[k].lower = nodes[k].upper = nullptr;
-    NetGuard net;
-    {
-      const int rc = gcp_net_create(&sub, &net.p);
-      if (rc != GCP_OK) return rc;
-    }
-    // CROWN-adaptive lower slopes of the prefix's unstable neurons (in alpha
-    // row order: node by node, ascending neuron index)
-    std::vector<float> arow;
-    for (int i = 0; i < k; ++i)
-      for (size_t j = 0; j < L[i].size(); ++j)
-        if (L[i][j] < 0.0 && U[i][j] > 0.0) arow.push_back(U[i][j] >= -L[i][j] ? 1.f : 0.f);
-    const size_t nI = arow.size();
-    // splits of earlier nodes whose neuron is unstable under the bounds found
-    // so far (a stable one already takes the piece its bounds allow)
-    std::vector<int32_t> sn, sj;
-    std::vector<int8_t> ss;
-    for (int s = 0; s < n_split; ++s) {
-      const int i = split_node[s], j = split_neuron[s];
-      if (i < k && L[i][j] < 0.0 && U[i][j] > 0.0) {
-        sn.push_back(i);
-        sj.push_back(j);
-        ss.push_back(split_sign[s]);
-      }
-    }
-    const int K = (int)sn.size();
-    SplitsGuard spl;
-    {
-      const int rc = gcp_splits_create(net.p, 1, K, sn.data(), sj.data(), ss.data(), &spl.p);
-      if (rc != GCP_OK) return rc;
-    }
-    // spec rows: +e_j (lower bound of x_j) then -e_j (minus the upper bound)
-    const int S_all = 2 * d;
-    const int rows = std::min(kRowsPerCall, S_all);
-    DBuf Cd, Ad, Bd, Zd;   // Zd: the split multipliers, all 0
-    Cd.alloc((size_t)rows * d * 8);
-    if (K) Zd.alloc((size_t)rows * K * 4);
-    Ad.alloc(std::max<size_t>((size_t)rows * nI * 4, 4));
-    Bd.alloc((size_t)rows * 8);
-    if (nI) {
-      hip_check(hipMemcpyAsync(Ad.p, arow.data(), nI * 4, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
-      hip_check(launch_repeat_row(Ad.as<float>(), rows, (int)nI, st), "slope rows");
-    }
-    std::vector<double> bh(rows);
     std::vector<double> lo(d), hi(d);
-    for (int s0 = 0; s0 < S_all; s0 += rows) {
-      const int S = std::min(rows, S_all - s0);
-      hip_check(launch_unit_rows(Cd.as<double>(), S, d, s0, st), "unit spec rows");
-      const int rc = gcp_bound(net.p, x0, eps, Cd.as<double>(), S, spl.p, nullptr, nI ? Ad.as<float>() : nullptr,
-                               K ? Zd.as<float>() : nullptr, nullptr, mode & (0xff | GCP_FLAG_OUTWARD),
-                               Bd.as<double>(), nullptr, nullptr,
-                               nullptr, nullptr, stream);
-      if (rc != GCP_OK) return rc;
-      hip_check(hipMemcpyAsync(bh.data(), Bd.p, (size_t)S * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-      hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
-      for (int r = 0; r < S; ++r) {
-        const int g = s0 + r;
-        if (g < d) lo[g] = bh[r];
-        else hi[g - d] = -bh[r];
+    auto prefix = [&]() -> int {
+      try {
+        // the prefix network: nodes 0..k with node k as its output (the
+        // pre-activation), earlier nodes carrying the bounds found so far
+        gcp_net_desc sub{desc->in_c, desc->in_h, desc->in_w, k + 1, nodes.data()};
+        for (int i = 0; i < k; ++i) {
+          nodes[i].lower = L[i].data();
+          nodes[i].upper = U[i].data();
+        }
+        nodes[k] = nk;
+        nodes[k].lower = nodes[k].upper = nullptr;
+        NetGuard net;
+        {
+          const int rc = gcp_net_create(&sub, &net.p);
+          if (rc != GCP_OK) return rc;
+        }
+        // CROWN-adaptive lower slopes of the prefix's unstable neurons (in alpha
+        // row order: node by node, ascending neuron index)
+        std::vector<float> arow;
+        for (int i = 0; i < k; ++i)
+          for (size_t j = 0; j < L[i].size(); ++j)
+            if (L[i][j] < 0.0 && U[i][j] > 0.0) arow.push_back(U[i][j] >= -L[i][j] ? 1.f : 0.f);
+        const size_t nI = arow.size();
+        // splits of earlier nodes whose neuron is unstable under the bounds found
+        // so far (a stable one already takes the piece its bounds allow)
+        std::vector<int32_t> sn, sj;
+        std::vector<int8_t> ss;
+        for (int s = 0; s < n_split; ++s) {
+          const int i = split_node[s], j = split_neuron[s];
+          if (i < k && L[i][j] < 0.0 && U[i][j] > 0.0) {
+            sn.push_back(i);
+            sj.push_back(j);
+            ss.push_back(split_sign[s]);
+          }
+        }
+        const int K = (int)sn.size();
+        SplitsGuard spl;
+        {
+          const int rc = gcp_splits_create(net.p, 1, K, sn.data(), sj.data(), ss.data(), &spl.p);
+          if (rc != GCP_OK) return rc;
+        }
+        // spec rows: +e_j (lower bound of x_j) then -e_j (minus the upper bound)
+        const int S_all = 2 * d;
+        const int rows = std::min(kRowsPerCall, S_all);
+        DBuf Cd, Ad, Bd, Zd;   // Zd: the split multipliers, all 0
+        Cd.alloc((size_t)rows * d * 8);
+        if (K) Zd.alloc((size_t)rows * K * 4);
+        Ad.alloc(std::max<size_t>((size_t)rows * nI * 4, 4));
+        Bd.alloc((size_t)rows * 8);
+        if (nI) {
+          hip_check(hipMemcpyAsync(Ad.p, arow.data(), nI * 4, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+          hip_check(launch_repeat_row(Ad.as<float>(), rows, (int)nI, st), "slope rows");
+        }
+        std::vector<double> bh(rows);
+        for (int s0 = 0; s0 < S_all; s0 += rows) {
+          const int S = std::min(rows, S_all - s0);
+          hip_check(launch_unit_rows(Cd.as<double>(), S, d, s0, st), "unit spec rows");
+          const int rc = gcp_bound(net.p, x0, eps, Cd.as<double>(), S, spl.p, nullptr, nI ? Ad.as<float>() : nullptr,
+                                   K ? Zd.as<float>() : nullptr, nullptr, mode & (0xff | GCP_FLAG_OUTWARD),
+                                   Bd.as<double>(), nullptr, nullptr,
+                                   nullptr, nullptr, stream);
+          if (rc != GCP_OK) return rc;
+          hip_check(hipMemcpyAsync(bh.data(), Bd.p, (size_t)S * 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+          hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");
+          for (int r = 0; r < S; ++r) {
+            const int g = s0 + r;
+            if (g < d) lo[g] = bh[r];
+            else hi[g - d] = -bh[r];
+          }
+        }
+        return GCP_OK;
+      } catch (const Err& e) {
+        g_err = e.msg;
+        return e.code;
       }
-    }
+    };
+    scope.arena.rewind();    // (the last bounds of node k - 1 were waited for)
+    const int rc = in_arena(scope, GCP_ENOMEM, prefix);
+    if (rc != GCP_OK) return rc;
     for (int j = 0; j < d; ++j) {
       if (!std::isfinite(lo[j]) || !std::isfinite(hi[j]))
         fail(GCP_ENONFINITE, "non-finite intermediate bound at node " + std::to_string(k));
