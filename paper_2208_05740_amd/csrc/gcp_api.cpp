@@ -1606,6 +1606,13 @@ struct BoundPass {
   BoundPass(Call& cc, int b, bool k, bool wc, bool d) : c(cc), bf16(b), keep_ahat(k), want_contrib(wc), dry(d) {}
 
   int esz() const { return bf16 ? 2 : 4; }
+  // operand bytes of node p's relaxation beside its GEMM's operands, and of a launch's row partials
+  double slot_bytes(int nslot) const { return sums ? (double)c.M * nslot * 8 : 0.0; }
+  double relax_bytes(const BoundEpiArgs& a, int p) const {
+    const double M = c.M, d = a.nd.size, nu = unst_of(c, p);
+    return M * d * esz() + (a.ahat_out ? M * nu * esz() : 0.0) + M * nu * (a.rp.rho ? 8 : 4) + (double)c.B * nu +
+           M * nnz_of(c, p) * 4 + (a.acc_in ? M * d * (a.acc_t ? esz() : 4) : 0.0);
+  }
   double* partial() const { return sums ? c.ws->partial.as<double>() : nullptr; }
 
   BoundEpiArgs bound_args(int p, bool has_acc) {
@@ -1660,9 +1667,7 @@ struct BoundPass {
       pushes_left[p]--;
       BoundEpiArgs a = bound_args(p, false);
       int nslot = slots_for_elementwise(net->nodes[p].size);
-      const double M = c.M, d = net->nodes[p].size, esz = bf16 ? 2 : 4;
-      const double bytes = c.S * d * 4 + M * d * esz + (keep_ahat ? M * d * esz : 0) + M * unst_of(c, p) * 4 +
-                           (double)c.B * unst_of(c, p) + M * nnz_of(c, p) * 4 + M * nslot * 8;
+      const double bytes = c.S * (double)net->nodes[p].size * 4 + relax_bytes(a, p) + slot_bytes(nslot);
       if (!dry && c.rec) {
         Rec r{};
         r.type = 1; r.bf16 = bf16; r.cfg = -1; r.kind = EPI_BOUND; r.sign = 0;
@@ -1744,10 +1749,8 @@ struct BoundPass {
                                pi ? pi_dense_cands(g.M, g.N) : dense_cands(g.M, g.N),
                                [&](int cf) { return launch_gemm(bf16, cf, EPI_BOUND, gt, &a, c.st); });
           g.partial = partial(); g.slot0 = slot;
-          const double M = g.M, esz = bf16 ? 2 : 4, dp = g.N;
-          const double bytes = M * g.K * esz + (double)g.N * g.K * esz + M * dp * esz + (keep_ahat ? M * dp * esz : 0) +
-                               M * unst_of(c, p) * (pi ? 8 : 4) + (double)c.B * unst_of(c, p) + M * nnz_of(c, p) * 4 +
-                               (has_acc ? M * dp * 4 : 0) + M * nslot * 8;
+          const double M = g.M, esz = bf16 ? 2 : 4;
+          const double bytes = M * g.K * esz + (double)g.N * g.K * esz + relax_bytes(a, p) + slot_bytes(nslot);
           if (!record_gemm(c, bf16, cfg, EPI_BOUND, g, a, Bytes{bytes, alg_bound(c, p)}))
             check(timed(c.st, pi ? cls_name("bound_pi", bf16, 0, pi_cfg(cfg)) : cls_name("bound", bf16, 0, cfg),
                         Bytes{bytes, alg_bound(c, p)},
@@ -1769,7 +1772,7 @@ struct BoundPass {
           g.partial = partial(); g.slot0 = slot;
           const double M = g.M, esz = bf16 ? 2 : 4;
           const double bytes = M * g.K * esz + (double)g.N * g.K * esz + (keep_ahat ? M * g.N : 0) +
-                               M * nnz_of(c, -1) * 4 * (want_contrib ? 2 : 1) + M * nslot * 8;
+                               M * nnz_of(c, -1) * 4 * (want_contrib ? 2 : 1) + slot_bytes(nslot);
           if (!record_gemm(c, bf16, cfg, EPI_CONC, g, a, Bytes{bytes, 0.0}))
             check(timed(c.st, cls_name("conc", bf16, 0, cfg), Bytes{bytes, 0.0}, 2.0 * g.M * g.N * g.K,
                         [&] { return launch_gemm(bf16, cfg, EPI_CONC, g, &a, c.st); }));
@@ -1816,9 +1819,7 @@ struct BoundPass {
                                [&](int cf) { return launch_conv(bf16, cf, EPI_BOUND, ca, &a, c.st); });
           ConvArgs cr = ca;
           cr.partial = partial(); cr.slot0 = slot;
-          const double bytes = M * dn.size * esz + wbytes + M * d_src * esz + (keep_ahat ? M * d_src * esz : 0) +
-                               M * unst_of(c, p) * (pi ? 8 : 4) + (double)c.B * unst_of(c, p) + M * nnz_of(c, p) * 4 +
-                               (has_acc ? M * d_src * 4 : 0) + M * nslot * 8;
+          const double bytes = M * dn.size * esz + wbytes + relax_bytes(a, p) + slot_bytes(nslot);
           check(timed(c.st, cls_name(pi ? "convT_bound_pi" : "convT_bound", bf16, 0, -1), Bytes{bytes, alg_bound(c, p)},
                       flops,
                       [&] { return launch_conv(bf16, cfg, EPI_BOUND, cr, &a, c.st); }));
@@ -1837,7 +1838,7 @@ struct BoundPass {
           ConvArgs cr = ca;
           cr.partial = partial(); cr.slot0 = slot;
           const double bytes = M * dn.size * esz + wbytes + (keep_ahat ? M * d_src : 0) +
-                               M * nnz_of(c, -1) * 4 * (want_contrib ? 2 : 1) + M * nslot * 8;
+                               M * nnz_of(c, -1) * 4 * (want_contrib ? 2 : 1) + slot_bytes(nslot);
           check(timed(c.st, cls_name("convT_conc", bf16, 0, -1) + (cfg == kConvDirectCfg ? ".direct" : ""),
                       Bytes{bytes, 0.0}, flops,
                       [&] { return launch_conv(bf16, cfg, EPI_CONC, cr, &a, c.st); }));
@@ -1862,7 +1863,8 @@ struct BoundPass {
       BoundEpiArgs a = bound_args(p, has_acc);
       const int nslot = slots_for_elementwise(d_src);
       if (!dry)
-        check(timed(c.st, cls_name("bound_elem", bf16, 0, -1), Bytes{(double)c.M * d_src * 16, alg_bound(c, p)}, 0.0, [&] {
+        check(timed(c.st, cls_name("bound_elem", bf16, 0, -1),
+                    Bytes{(double)c.M * d_src * esz() + relax_bytes(a, p) + slot_bytes(nslot), alg_bound(c, p)}, 0.0, [&] {
           return launch_bound_elementwise(bf16, nullptr, ws.lam[E.dst]->p, a, partial(), slot, c.st);
         }));
       slot += nslot;
@@ -1942,7 +1944,7 @@ struct AdjPass {
       g.mp = c.rp.mp;
       const int cfg = choose_cfg("gemm", EPI_BOUND, bf16, 0, g.M, g.N, g.K, c.st, dense_cands(g.M, g.N),
                                  [&](int cf) { return launch_gemm(bf16, cf, EPI_AHAT, g, &a, c.st); });
-      const double bytes = M * g.K * esz + (double)g.N * g.K * esz + M * g.N * esz + M * nnz_of(c, i) * 4;
+      const double bytes = M * g.K * esz + (double)g.N * g.K * esz + M * unst_of(c, i) * esz + M * nnz_of(c, i) * 4;
       check(timed(c.st, cls_name("ahat", bf16, 0, cfg), Bytes{bytes, 0.0}, 2.0 * g.M * g.N * g.K,
                   [&] { return launch_gemm(bf16, cfg, EPI_AHAT, g, &a, c.st); }));
     } else {
@@ -1957,7 +1959,7 @@ struct AdjPass {
       const int cfg = choose_cfg("convT", EPI_BOUND, bf16, 0, c.M, E.d_src, dn.size, c.st, conv_cands(),
                                  [&](int cf) { return launch_conv(bf16, cf, EPI_AHAT, ca, &a, c.st); });
       const double bytes = M * dn.size * esz + (double)cg.stride * cg.stride * cg.ci * E.ldk_t * esz +
-                           M * E.d_src * esz + M * nnz_of(c, i) * 4;
+                           M * unst_of(c, i) * esz + M * nnz_of(c, i) * 4;
       check(timed(c.st, cls_name("convT_ahat", bf16, 0, -1), Bytes{bytes, 0.0},
                   2.0 * M * cg.ho * cg.wo * cg.ci * cg.co * cg.kh * cg.kw,
                   [&] { return launch_conv(bf16, cfg, EPI_AHAT, ca, &a, c.st); }));
@@ -1987,8 +1989,9 @@ struct AdjPass {
     const bool use_acc = order.size() > 1 || !fused_last;
     const double M = c.M, esz = bf16 ? 2 : 4, di = n.size;
     auto adj_bytes = [&](double a_bytes, double w_bytes) {
-      return a_bytes + w_bytes + M * di * esz + M * unst_of(c, i) * (adam.enabled ? 24 : 8) * (pi ? 2 : 1) +
-             (double)c.B * unst_of(c, i) + M * nnz_of(c, i) * 8 + M * di * esz + (use_acc ? M * di * 4 : 0);
+      return a_bytes + w_bytes + M * unst_of(c, i) * esz + M * unst_of(c, i) * (adam.enabled ? 24 : 8) * (pi ? 2 : 1) +
+             (double)c.B * unst_of(c, i) + M * nnz_of(c, i) * 8 + M * di * esz +
+             (use_acc ? M * di * (acc_rd == accbuf ? 4 : esz) : 0);
     };
     for (size_t q = 0; q < order.size(); ++q) {
       const EdgeH& E = *net->edges[order[q]];
@@ -2488,7 +2491,7 @@ void run_chain(Call& c, int bf16, const ChainPlan& pl, float* alpha, float* beta
   auto& ws = *c.ws;
   const int L = net->out;
   ws.chain_host.resize(L);
-  double flops = 0.0, elems = 0.0;
+  double flops = 0.0;
   for (int i = 0; i < L; ++i) {
     const NodeH& n = net->nodes[i];
     const EdgeH& E = *net->edges[n.in_edges[0]];
@@ -2503,7 +2506,6 @@ void run_chain(Call& c, int bf16, const ChainPlan& pl, float* alpha, float* beta
     cn.ahat = ws.ahat[i]->p;
     cn.dahat = ws.dahat[i]->p;
     flops += 4.0 * c.M * E.d_src * E.d_dst;   // the bound-pass and adjoint GEMM of the in-edge
-    elems += n.size;
   }
   ws.chain_tab.ensure(sizeof(ChainNode) * L);
   hip_check(hipMemcpyAsync(ws.chain_tab.p, ws.chain_host.data(), sizeof(ChainNode) * L, hipMemcpyHostToDevice, c.st),
@@ -2537,7 +2539,7 @@ void run_chain(Call& c, int bf16, const ChainPlan& pl, float* alpha, float* beta
   a.sign_ld = pl.sign_ld;
   const double M = c.M, it = opt->iters, nI = c.rp.n_I, N = c.rp.N, K = c.rp.K, nnz = c.nnz;
   const double alg = it * (28.0 * M * (nI + N + K) + 2.0 * c.B * nI);
-  const double all = it * (M * (nI * 28.0 + elems * 2.0 * esz + nnz * 12.0 + N * 24.0 + K * 28.0) + 2.0 * c.B * nI);
+  const double all = it * (M * (nI * (28.0 + 2.0 * esz) + nnz * 12.0 + N * 24.0 + K * 28.0) + 2.0 * c.B * nI);
   const int tiles = (c.M + kChainRows - 1) / kChainRows;
   hip_check(timed(c.st, std::string("chain.") + (bf16 ? "bf16" : "fp32"), Bytes{all, alg}, it * flops,
                   [&] { return launch_chain_opt(bf16, a, tiles, pl.lds, c.st); }),
