@@ -19,6 +19,10 @@ SHAPES = [
     (0, (2, 8, 8), ((320, 1, 1, 0), (64, 3, 1, 1))),      # fp32: the adjoint's slab fits, but not with its tables
     (1, (2, 8, 8), ((320, 1, 1, 0), (64, 3, 1, 1))),
     (0, (2, 4, 4), ((512, 1, 1, 0), (64, 3, 1, 1))),
+    (0, (2, 32, 32), ((64, 1, 1, 0), (32, 5, 1, 2))),     # one batch row in the slab, more than 64 KB with its results
+    (0, (2, 32, 32), ((64, 3, 1, 1), (64, 3, 1, 1))),
+    (0, (128, 64, 64), ((32, 1, 1, 0),)),                 # the transposed direction into the input, 142 KB
+    (1, (128, 64, 64), ((32, 1, 1, 0),)),
 ]
 
 
