@@ -3049,15 +3049,6 @@ long instance_work(const gcp_batch_item& it) {
   for (const NodeH& nd : it.net->nodes) width = std::max(width, nd.ld);
   return (long)it.splits->B * it.S * width;
 }
-// Whether a net's rows may be too long for the 32-bit offsets of a grouped
-// launch's tiles (64 rows of four bytes an element within 2 GiB): the net then
-// runs on its own launches, which choose by their sizes.
-bool rows_too_long_to_group(const gcp_net* net) {
-  if (!net) return false;
-  int widest = std::max(net->in_ld, net->n_I);
-  for (const NodeH& nd : net->nodes) widest = std::max(widest, nd.ld);
-  return widest >= 1 << 23;
-}
 // Grouped launches replay a recorded schedule of dense GEMMs with fused
 // epilogues: conv and identity edges and a materialised output Lambda have no
 // recorded form.  Returns what stands in the way, or null.
@@ -3067,6 +3058,15 @@ const char* grouped_unsupported(const gcp_net* net) {
     if (e->kind == GCP_EDGE_IDENTITY) return "identity";
   }
   return net->out_general ? "output Lambda not in the c-hat form" : nullptr;
+}
+// Whether the rows of a net that could be grouped may be too long for the
+// 32-bit offsets of a grouped launch's tiles (64 rows of four bytes an element
+// within 2 GiB): it then runs on its own launches, which choose by their sizes.
+bool rows_too_long_to_group(const gcp_net* net) {
+  if (grouped_unsupported(net)) return false;
+  int widest = std::max(net->in_ld, net->n_I);
+  for (const NodeH& nd : net->nodes) widest = std::max(widest, nd.ld);
+  return widest >= 1 << 23;
 }
 }  // namespace
 
@@ -3089,7 +3089,7 @@ extern "C" int gcp_optimize_batch(int32_t n_all, const gcp_batch_item* items_all
   // with GCP_FLAG_PERSIST every instance shares the one persistent launch
   // (measured: keeping the large instances on their own launches beside it
   // is slower still, since the persistent grid holds every compute unit
-  // until its queues drain)
+  // until its queues drain); those with rows too long to group run per layer
   const long alone = (mode & GCP_FLAG_PERSIST) ? std::numeric_limits<long>::max() : batch_alone_work();
   std::vector<gcp_batch_item> grouped;
   std::vector<std::pair<long, int>> big;
@@ -3139,7 +3139,7 @@ extern "C" int gcp_optimize_batch(int32_t n_all, const gcp_batch_item* items_all
       load[k] += (double)b.first;
       const gcp_batch_item& it = items_all[b.second];
       rc = gcp_optimize(it.net, it.x0, it.eps, it.C, it.S, it.splits, it.cuts, it.alpha, it.beta, it.gamma,
-                        it.adam_state, opt, mode, it.bound, it.verified, ss[k]);
+                        it.adam_state, opt, mode & ~GCP_FLAG_PERSIST, it.bound, it.verified, ss[k]);
       if (rc != GCP_OK) break;
     }
     if (ns > 1) {   // the caller's stream waits for every side stream
